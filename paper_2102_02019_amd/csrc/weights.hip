@@ -1280,6 +1280,98 @@ __device__ __forceinline__ KernargBuildArgs* build_args_again() {
   return p;
 }
 
+// Adds node (xi, yi)'s neighbours to the moment-matrix tiles (P, Q0 + Q), P <
+// NB, Q < QN, accumulated by one wavefront: the basis tables of kChunk
+// neighbours at a time in T (LDS), then the chunk's MFMA steps. (ea, eb): the
+// exponents of this lane's moment index in each tile, -1 past n.
+template <int M, int NB, int QG>
+__device__ __forceinline__ void assemble_tiles(const BuildArgs& g, int e0, int K, double xi,
+                                               double yi, double hinv, const int (&ea)[NB],
+                                               const int (&eb)[NB], int Q0, int QN, double* T,
+                                               double4_t (&acc)[NB][QG]) {
+  using S = RowShape<M>;
+  constexpr int TW = S::TW;
+  const int lane = threadIdx.x;
+  const int kk = lane >> 2, t = lane & 3;  // table lanes: neighbour kk, table t
+  // coordinates of the lane's neighbour one chunk ahead
+  double xn = 0.0, yn = 0.0;
+  if (kk < K) {
+    const int j = g.col[e0 + kk];
+    xn = g.x[j];
+    yn = g.y[j];
+  }
+  if (lane < kChunk) T[lane * S::TABLE + S::ZERO] = 0.0;
+  for (int k0 = 0; k0 < K; k0 += kChunk) {
+    const bool have = k0 + kk < K;
+    const double xj = xn, yj = yn;
+    if (k0 + kChunk + kk < K) {  // the next chunk's coordinates, in flight meanwhile
+      const int j = g.col[e0 + k0 + kChunk + kk];
+      xn = g.x[j];
+      yn = g.y[j];
+    }
+    double* tab = &T[kk * S::TABLE + t * TW];
+    if (have) {
+      const double dx = wrap_axis(xj - xi, g.box.Lx, g.box.periodic_x);
+      const double dy = wrap_axis(yj - yi, g.box.Ly, g.box.periodic_y);
+      const double xs = dx * hinv, ys = dy * hinv;
+      const double z = (t == 0 || t == 2) ? xs : ys;
+      if (t < 2) {
+        double v = 1.0;
+        tab[0] = 1.0;
+#pragma unroll
+        for (int a2 = 1; a2 <= M; ++a2) {
+          v = v * z * (1.0 / static_cast<double>(a2));  // z^a / a!
+          tab[a2] = v;
+        }
+      } else {
+        const double psi = (t == 2) ? wendland_c2(sqrt(xs * xs + ys * ys)) : 1.0;
+        double h0 = 1.0, h1 = z;
+        tab[0] = psi;
+        if (M >= 1) tab[1] = psi * z;
+#pragma unroll
+        for (int a2 = 1; a2 < M; ++a2) {
+          const double h2 = z * h1 - static_cast<double>(a2) * h0;
+          h0 = h1;
+          h1 = h2;
+          tab[a2 + 1] = psi * h2;
+        }
+      }
+    } else {
+#pragma unroll
+      for (int a2 = 0; a2 <= M; ++a2) tab[a2] = 0.0;
+    }
+    lds_barrier();
+#pragma unroll
+    for (int ks = 0; ks < kChunk / 4; ++ks) {
+      // steps of the last chunk past the K neighbours add only zeros
+      if (k0 + ks * 4 >= K) break;
+      const double* tk = &T[(ks * 4 + (lane >> 4)) * S::TABLE];
+      double av[NB], bv[QG];
+#pragma unroll
+      for (int P = 0; P < NB; ++P) {
+        const int oa = ea[P] >= 0 ? ea[P] : S::ZERO, ob = ea[P] >= 0 ? TW + eb[P] : S::ZERO;
+        av[P] = tk[oa] * tk[ob];
+      }
+#pragma unroll
+      for (int Q = 0; Q < QG; ++Q) {
+        if (Q < QN) {
+          const int P = Q0 + Q;
+          const int oc = ea[P] >= 0 ? 2 * TW + ea[P] : S::ZERO;
+          const int od = ea[P] >= 0 ? 3 * TW + eb[P] : S::ZERO;
+          bv[Q] = tk[oc] * tk[od];
+        }
+      }
+#pragma unroll
+      for (int P = 0; P < NB; ++P)
+#pragma unroll
+        for (int Q = 0; Q < QG; ++Q)
+          if (Q < QN)
+            acc[P][Q] = __builtin_amdgcn_mfma_f64_16x16x4f64(av[P], bv[Q], acc[P][Q], 0, 0, 0);
+    }
+    lds_barrier();
+  }
+}
+
 // Systems given to the rows kernel's LU and back substitution directly (its
 // solve variant): row r of system k at sys + (k n + r)(n + 6), its n values
 // of M~, then its six of C~.
@@ -1291,6 +1383,240 @@ struct SolveArgs {
   int8_t* status = nullptr;  // [k]: LABFM_NODE_OK or LABFM_NODE_SINGULAR
 };
 
+// Step 5 of the rows kernels for node i (row e0 .. e0 + K of the CSR): one lane
+// per neighbour; Psi read from LDS a row at a time (the lanes' reads of one
+// row are a broadcast; rows of NOPS values at an even stride). The arguments
+// and the node's position, scale and spacing are read again here (see
+// build_args_again). With three operators (x, y, L) the weights and the status
+// alone are written.
+template <int NOPS>
+constexpr int psi_stride() {
+  return (NOPS + 1) & ~1;
+}
+template <int M, int NOPS>
+__device__ __forceinline__ void node_weights(int i, int e0, int K, int st,
+                                             const double* psi_t) {
+  constexpr int N = RowShape<M>::N, PST = psi_stride<NOPS>();
+  constexpr bool kFull = NOPS == LABFM_NUM_OPS;
+  static_assert(kFull || NOPS == 3, "all operators, or x, y and L");
+  const int lane = threadIdx.x;
+  KernargBuildArgs* ga = build_args_again();
+  const double xw = ga->x[i], yw = ga->y[i], hinvw = 1.0 / ga->h[i];
+  const int pxw = ga->box.periodic_x, pyw = ga->box.periodic_y;
+  const double kf = kFull ? 2.0 * M_PI / (3.0 * ga->s[i]) : 0.0;
+  double f0 = 0.0;
+  double rs[LABFM_NUM_OPS] = {0.0, 0.0, 0.0, 0.0, 0.0, 0.0};
+  double mo[kMoments] = {0.0, 0.0, 0.0, 0.0, 0.0, 0.0};
+  const long long s32 = w32_stride(ga->nnz);
+  // offsets of neighbour k and its Hermite ABF factors: hx[a] = psi He_a(x),
+  // hy[b] = He_b(y) (scaled offsets)
+  auto basis_of = [&](int k, double& dx, double& dy, double* hx, double* hy) {
+    const int j = ga->col[e0 + k];
+    dx = wrap_axis(ga->x[j] - xw, ga->box.Lx, pxw);
+    dy = wrap_axis(ga->y[j] - yw, ga->box.Ly, pyw);
+    const double xs = dx * hinvw, ys = dy * hinvw;
+    const double psi = wendland_c2(sqrt(xs * xs + ys * ys));
+    hx[0] = psi;
+    hy[0] = 1.0;
+    hx[1] = psi * xs;
+    hy[1] = ys;
+    double a0 = 1.0, a1 = xs, b0 = 1.0, b1 = ys;
+#pragma unroll
+    for (int q = 1; q < M; ++q) {
+      const double a2 = xs * a1 - static_cast<double>(q) * a0;
+      const double b2 = ys * b1 - static_cast<double>(q) * b0;
+      a0 = a1;
+      a1 = a2;
+      b0 = b1;
+      b1 = b2;
+      hx[q + 1] = psi * a2;
+      hy[q + 1] = b2;
+    }
+  };
+  // full passes of 64 neighbours, then a last pass over at most 32
+  // neighbours in which lanes l and l + 32 share neighbour k0 + l, the
+  // first forming operators x, y, L, the second xx, xy, hyp (og = 0, 1)
+  int k0 = 0;
+  for (; K - k0 > (kFull ? 32 : 0); k0 += 64) {
+    const int k = k0 + lane;
+    // Psi's offset passes through an empty asm statement every pass, so the
+    // compiler does not hoist all of its reads out of the loop (n * 6
+    // values held in registers)
+    int pbase = 0;
+    asm volatile("" : "+v"(pbase));
+    if (k < K) {
+      double dx, dy, hx[M + 1], hy[M + 1];
+      basis_of(k, dx, dy, hx, hy);
+      const long long e = e0 + k;
+      double wd[NOPS] = {};
+      // Psi row q in registers, row q+1 read from LDS while q is used
+      double r0[NOPS], r1[NOPS];
+#pragma unroll
+      for (int d = 0; d < NOPS; ++d) r0[d] = psi_t[pbase + d];
+#pragma unroll
+      for (int deg = 1, q = 0; deg <= M; ++deg) {
+#pragma unroll
+        for (int bb = 0; bb <= deg; ++bb, ++q) {
+          if (q + 1 < N) {
+#pragma unroll
+            for (int d = 0; d < NOPS; ++d)
+              r1[d] = psi_t[pbase + (q + 1) * PST + d];
+          }
+          const double Wq = hx[deg - bb] * hy[bb];
+#pragma unroll
+          for (int d = 0; d < NOPS; ++d) {
+            wd[d] = fma(Wq, r0[d], wd[d]);
+            pin(wd[d]);
+          }
+#pragma unroll
+          for (int d = 0; d < NOPS; ++d) r0[d] = r1[d];
+        }
+      }
+#pragma unroll
+      for (int d = 0; d < NOPS; ++d) {
+        const int r = op_row(ga->rows, d);
+        if (r != kNoRow) {
+          ga->w[r * ga->nnz + e] = wd[d];
+          if (ga->w32) ga->w32[r * s32 + e] = static_cast<float>(wd[d]);
+        }
+        rs[d] += wd[d];
+      }
+      if constexpr (kFull) {
+#pragma unroll
+        for (int d = LABFM_OP_L; d <= LABFM_OP_XY; ++d) {
+          const double v32 = static_cast<double>(static_cast<float>(wd[d]));
+          mo[2 * (d - LABFM_OP_L)] += v32 * dx;
+          mo[2 * (d - LABFM_OP_L) + 1] += v32 * dy;
+        }
+        f0 += (1.0 - cos(kf * dx) * cos(kf * dy)) * wd[LABFM_OP_HYP];
+      }
+    }
+  }
+  if constexpr (kFull) {
+    if (k0 < K) {
+      const int k = k0 + (lane & 31);
+      const int og = lane >> 5;
+      int pbase = 0;
+      asm volatile("" : "+v"(pbase));
+      if (k < K) {
+        double dx, dy, hx[M + 1], hy[M + 1];
+        basis_of(k, dx, dy, hx, hy);
+        const long long e = e0 + k;
+        constexpr int H3 = LABFM_NUM_OPS / 2;
+        static_assert(LABFM_OP_L == 2 && LABFM_OP_XX == 3 && LABFM_OP_XY == 4 &&
+                          LABFM_OP_HYP == 5,
+                      "operator groups of a half pass: (x, y, L), (xx, xy, hyp)");
+        const int ob = pbase + og * H3;  // this lane's operators in a Psi row
+        double wd[H3] = {0.0, 0.0, 0.0};
+        double r0[H3], r1[H3];
+#pragma unroll
+        for (int d = 0; d < H3; ++d) r0[d] = psi_t[ob + d];
+#pragma unroll
+        for (int deg = 1, q = 0; deg <= M; ++deg) {
+#pragma unroll
+          for (int bb = 0; bb <= deg; ++bb, ++q) {
+            if (q + 1 < N) {
+#pragma unroll
+              for (int d = 0; d < H3; ++d) r1[d] = psi_t[ob + (q + 1) * PST + d];
+            }
+            const double Wq = hx[deg - bb] * hy[bb];
+#pragma unroll
+            for (int d = 0; d < H3; ++d) {
+              wd[d] = fma(Wq, r0[d], wd[d]);
+              pin(wd[d]);
+            }
+#pragma unroll
+            for (int d = 0; d < H3; ++d) r0[d] = r1[d];
+          }
+        }
+#pragma unroll
+        for (int d = 0; d < H3; ++d) {
+          const int r = op_row(ga->rows, og * H3 + d);
+          if (r != kNoRow) {
+            ga->w[r * ga->nnz + e] = wd[d];
+            if (ga->w32) ga->w32[r * s32 + e] = static_cast<float>(wd[d]);
+          }
+          // each sum takes this lane's value for its own operators only
+          rs[d] += og ? 0.0 : wd[d];
+          rs[H3 + d] += og ? wd[d] : 0.0;
+        }
+        // L is the first group's third operator, xx and xy the second's
+        // first two, hyp its third
+        const double vl = og ? 0.0 : static_cast<double>(static_cast<float>(wd[2]));
+        const double vxx = og ? static_cast<double>(static_cast<float>(wd[0])) : 0.0;
+        const double vxy = og ? static_cast<double>(static_cast<float>(wd[1])) : 0.0;
+        mo[0] += vl * dx;
+        mo[1] += vl * dy;
+        mo[2] += vxx * dx;
+        mo[3] += vxx * dy;
+        mo[4] += vxy * dx;
+        mo[5] += vxy * dy;
+        // one cosine per lane: the first half takes x, the second y and
+        // the x factor from its partner (lanes l and l + 32 share neighbour
+        // k and are active together); the second half holds hyp
+        const double cf = cos(kf * (og ? dy : dx));
+        const double cx = __shfl_xor(cf, 32);
+        f0 += og ? (1.0 - cx * cf) * wd[2] : 0.0;
+      }
+    }
+  }
+  if constexpr (!kFull) {
+    if (lane == 0) ga->status[i] = static_cast<int8_t>(st);
+    return;
+  }
+  f0 = group_sum<64>(f0);
+  // the row sums and first moments are reduced only when they are asked for
+  if (ga->rowsum) {
+#pragma unroll
+    for (int d = 0; d < LABFM_NUM_OPS; ++d) rs[d] = group_sum<64>(rs[d]);
+  }
+  if (ga->mom32) {
+#pragma unroll
+    for (int q = 0; q < kMoments; ++q) mo[q] = group_sum<64>(mo[q]);
+  }
+  if (lane == 0) {
+    if (ga->mom32)
+#pragma unroll
+      for (int q = 0; q < kMoments; ++q) ga->mom32[q * (long long)ga->n + i] = static_cast<float>(mo[q]);
+    const bool bad = !isfinite(f0) || f0 == 0.0;
+    ga->kappa[i] = bad ? 0.0 : 2.0 / (3.0 * f0);
+    if (st == LABFM_NODE_OK && bad) st = LABFM_NODE_BAD_FILTER;
+    ga->status[i] = static_cast<int8_t>(st);
+    if (ga->rowsum)
+#pragma unroll
+      for (int d = 0; d < LABFM_NUM_OPS; ++d)
+        if (op_row(ga->rows, d) != kNoRow) ga->rowsum[op_row(ga->rows, d) * (long long)ga->n + i] = rs[d];
+  }
+}
+
+// A singular node's outputs: zero weights, kappa, row sums and moments.
+template <int NOPS>
+__device__ __forceinline__ void node_singular(int i, int e0, int K) {
+  constexpr bool kFull = NOPS == LABFM_NUM_OPS;
+  const int lane = threadIdx.x;
+  KernargBuildArgs* ga = build_args_again();
+  const long long s32 = w32_stride(ga->nnz);
+  for (int k = lane; k < K; k += 64)
+    for (int d = 0; d < NOPS; ++d) {
+      const int r = op_row(ga->rows, d);
+      if (r == kNoRow) continue;
+      ga->w[r * ga->nnz + e0 + k] = 0.0;
+      if (ga->w32) ga->w32[r * s32 + e0 + k] = 0.0f;
+    }
+  if (lane == 0) {
+    ga->status[i] = LABFM_NODE_SINGULAR;
+    if constexpr (kFull) {
+      ga->kappa[i] = 0.0;
+      if (ga->rowsum)
+        for (int d = 0; d < LABFM_NUM_OPS; ++d)
+          if (op_row(ga->rows, d) != kNoRow)
+            ga->rowsum[op_row(ga->rows, d) * (long long)ga->n + i] = 0.0;
+      if (ga->mom32)
+        for (int q = 0; q < kMoments; ++q) ga->mom32[q * (long long)ga->n + i] = 0.0f;
+    }
+  }
+}
+
 // One wavefront's work of the rows kernel: node list[blockIdx.x]'s build or,
 // with kSolve, system blockIdx.x of sv through the same LU and back
 // substitution (steps 3 and 4) in place of the assembly and the weights.
@@ -1298,7 +1624,7 @@ template <int M, bool kSolve>
 __device__ __forceinline__ void rows_node(BuildArgs g, const int* __restrict__ list, int count,
                                           SolveArgs sv) {
   using S = RowShape<M>;
-  constexpr int N = S::N, NB = S::NB, RC = S::RC, TW = S::TW;
+  constexpr int N = S::N, NB = S::NB, RC = S::RC;
   __shared__ RowSmem<M> sm;
   const int k_ = blockIdx.x;
   if (k_ >= count) return;
@@ -1308,8 +1634,7 @@ __device__ __forceinline__ void rows_node(BuildArgs g, const int* __restrict__ l
   const int e0 = kSolve ? 0 : uniform(g.row_ptr[i]);
   const int K = kSolve ? N : uniform(g.row_ptr[i + 1]) - e0;
   const double xi = kSolve ? 0.0 : g.x[i], yi = kSolve ? 0.0 : g.y[i];
-  const double h = kSolve ? 1.0 : g.h[i], s = kSolve ? 1.0 : g.s[i];
-  const int px = g.box.periodic_x, py = g.box.periodic_y;
+  const double h = kSolve ? 1.0 : g.h[i];
   const double hinv = 1.0 / h;
   double* T = sm.buf;
 
@@ -1350,7 +1675,6 @@ __device__ __forceinline__ void rows_node(BuildArgs g, const int* __restrict__ l
     // two, each group moved into the rows before the next pass, so the
     // accumulators of all 25 tiles are never live at once.
     constexpr int QG = S::kExtra ? 3 : NB;
-    const int kk = lane >> 2, t = lane & 3;  // table lanes: neighbour kk, table t
     double* strip = sm.buf;  // the strips reuse the tables' LDS
     // Order 10: p0, the pivot row of column 0 (the largest |M~_r0| of the 65
     // rows, compared exactly, the lowest row on ties), is found in the first
@@ -1364,83 +1688,7 @@ __device__ __forceinline__ void rows_node(BuildArgs g, const int* __restrict__ l
       for (int P = 0; P < NB; ++P)
 #pragma unroll
         for (int Q = 0; Q < QG; ++Q) acc[P][Q] = double4_t{0.0, 0.0, 0.0, 0.0};
-      // coordinates of the lane's neighbour one chunk ahead
-      double xn = 0.0, yn = 0.0;
-      if (kk < K) {
-        const int j = g.col[e0 + kk];
-        xn = g.x[j];
-        yn = g.y[j];
-      }
-      if (lane < kChunk) T[lane * S::TABLE + S::ZERO] = 0.0;
-      for (int k0 = 0; k0 < K; k0 += kChunk) {
-        const bool have = k0 + kk < K;
-        const double xj = xn, yj = yn;
-        if (k0 + kChunk + kk < K) {  // the next chunk's coordinates, in flight meanwhile
-          const int j = g.col[e0 + k0 + kChunk + kk];
-          xn = g.x[j];
-          yn = g.y[j];
-        }
-        double* tab = &T[kk * S::TABLE + t * TW];
-        if (have) {
-          const double dx = wrap_axis(xj - xi, g.box.Lx, px);
-          const double dy = wrap_axis(yj - yi, g.box.Ly, py);
-          const double xs = dx * hinv, ys = dy * hinv;
-          const double z = (t == 0 || t == 2) ? xs : ys;
-          if (t < 2) {
-            double v = 1.0;
-            tab[0] = 1.0;
-#pragma unroll
-            for (int a2 = 1; a2 <= M; ++a2) {
-              v = v * z * (1.0 / static_cast<double>(a2));  // z^a / a!
-              tab[a2] = v;
-            }
-          } else {
-            const double psi = (t == 2) ? wendland_c2(sqrt(xs * xs + ys * ys)) : 1.0;
-            double h0 = 1.0, h1 = z;
-            tab[0] = psi;
-            if (M >= 1) tab[1] = psi * z;
-#pragma unroll
-            for (int a2 = 1; a2 < M; ++a2) {
-              const double h2 = z * h1 - static_cast<double>(a2) * h0;
-              h0 = h1;
-              h1 = h2;
-              tab[a2 + 1] = psi * h2;
-            }
-          }
-        } else {
-#pragma unroll
-          for (int a2 = 0; a2 <= M; ++a2) tab[a2] = 0.0;
-        }
-        lds_barrier();
-#pragma unroll
-        for (int ks = 0; ks < kChunk / 4; ++ks) {
-          // steps of the last chunk past the K neighbours add only zeros
-          if (k0 + ks * 4 >= K) break;
-          const double* tk = &T[(ks * 4 + (lane >> 4)) * S::TABLE];
-          double av[NB], bv[QG];
-#pragma unroll
-          for (int P = 0; P < NB; ++P) {
-            const int oa = ea[P] >= 0 ? ea[P] : S::ZERO, ob = ea[P] >= 0 ? TW + eb[P] : S::ZERO;
-            av[P] = tk[oa] * tk[ob];
-          }
-#pragma unroll
-          for (int Q = 0; Q < QG; ++Q) {
-            if (Q < QN) {
-              const int P = Q0 + Q;
-              const int oc = ea[P] >= 0 ? 2 * TW + ea[P] : S::ZERO;
-              const int od = ea[P] >= 0 ? 3 * TW + eb[P] : S::ZERO;
-              bv[Q] = tk[oc] * tk[od];
-            }
-          }
-#pragma unroll
-          for (int P = 0; P < NB; ++P)
-#pragma unroll
-            for (int Q = 0; Q < QG; ++Q)
-              if (Q < QN)
-                acc[P][Q] = __builtin_amdgcn_mfma_f64_16x16x4f64(av[P], bv[Q], acc[P][Q], 0, 0, 0);
-        }
-        lds_barrier();
-      }
+      assemble_tiles<M, NB, QG>(g, e0, K, xi, yi, hinv, ea, eb, Q0, QN, T, acc);
 
       // rows of this group's columns into registers, one 16-column strip at a
       // time; element v of lane l holds D[l/16 + 4v][l%16] of its 16x16 tile
@@ -1582,7 +1830,7 @@ __device__ __forceinline__ void rows_node(BuildArgs g, const int* __restrict__ l
     }
   }
 
-  int st = (K < N) ? LABFM_NODE_FEW_NEIGHBOURS : LABFM_NODE_OK;
+  const int st = (K < N) ? LABFM_NODE_FEW_NEIGHBOURS : LABFM_NODE_OK;
   if (!singular) {
     // ---- 4: back substitution ------------------------------------------------
     // each lane keeps its right-hand sides divided by its own pivot u_qq
@@ -1641,213 +1889,394 @@ __device__ __forceinline__ void rows_node(BuildArgs g, const int* __restrict__ l
       return;
     }
 
-    // ---- 5: weights, filter calibration, row sums, first moments -------------
-    // one lane per neighbour; Psi read from LDS a row at a time (the lanes'
-    // reads of one row are a broadcast). The arguments and the node's
-    // position, scale and spacing are read again here (see build_args_again).
-    KernargBuildArgs* ga = build_args_again();
-    const double xw = ga->x[i], yw = ga->y[i], hinvw = 1.0 / ga->h[i];
-    const int pxw = ga->box.periodic_x, pyw = ga->box.periodic_y;
-    const double kf = 2.0 * M_PI / (3.0 * ga->s[i]);
-    double f0 = 0.0;
-    double rs[LABFM_NUM_OPS] = {0.0, 0.0, 0.0, 0.0, 0.0, 0.0};
-    double mo[kMoments] = {0.0, 0.0, 0.0, 0.0, 0.0, 0.0};
-    const long long s32 = w32_stride(ga->nnz);
-    // offsets of neighbour k and its Hermite ABF factors: hx[a] = psi He_a(x),
-    // hy[b] = He_b(y) (scaled offsets)
-    auto basis_of = [&](int k, double& dx, double& dy, double* hx, double* hy) {
-      const int j = ga->col[e0 + k];
-      dx = wrap_axis(ga->x[j] - xw, ga->box.Lx, pxw);
-      dy = wrap_axis(ga->y[j] - yw, ga->box.Ly, pyw);
-      const double xs = dx * hinvw, ys = dy * hinvw;
-      const double psi = wendland_c2(sqrt(xs * xs + ys * ys));
-      hx[0] = psi;
-      hy[0] = 1.0;
-      hx[1] = psi * xs;
-      hy[1] = ys;
-      double a0 = 1.0, a1 = xs, b0 = 1.0, b1 = ys;
-#pragma unroll
-      for (int q = 1; q < M; ++q) {
-        const double a2 = xs * a1 - static_cast<double>(q) * a0;
-        const double b2 = ys * b1 - static_cast<double>(q) * b0;
-        a0 = a1;
-        a1 = a2;
-        b0 = b1;
-        b1 = b2;
-        hx[q + 1] = psi * a2;
-        hy[q + 1] = b2;
-      }
-    };
-    // full passes of 64 neighbours, then a last pass over at most 32
-    // neighbours in which lanes l and l + 32 share neighbour k0 + l, the
-    // first forming operators x, y, L, the second xx, xy, hyp (og = 0, 1)
-    int k0 = 0;
-    for (; K - k0 > 32; k0 += 64) {
-      const int k = k0 + lane;
-      // Psi's offset passes through an empty asm statement every pass, so the
-      // compiler does not hoist all of its reads out of the loop (n * 6
-      // values held in registers)
-      int pbase = 0;
-      asm volatile("" : "+v"(pbase));
-      if (k < K) {
-        double dx, dy, hx[M + 1], hy[M + 1];
-        basis_of(k, dx, dy, hx, hy);
-        const long long e = e0 + k;
-          double wd[LABFM_NUM_OPS] = {0.0, 0.0, 0.0, 0.0, 0.0, 0.0};
-        // Psi row q in registers, row q+1 read from LDS while q is used
-        double r0[LABFM_NUM_OPS], r1[LABFM_NUM_OPS];
-#pragma unroll
-        for (int d = 0; d < LABFM_NUM_OPS; ++d) r0[d] = psi_t[pbase + d];
-#pragma unroll
-        for (int deg = 1, q = 0; deg <= M; ++deg) {
-#pragma unroll
-          for (int bb = 0; bb <= deg; ++bb, ++q) {
-            if (q + 1 < N) {
-#pragma unroll
-              for (int d = 0; d < LABFM_NUM_OPS; ++d)
-                r1[d] = psi_t[pbase + (q + 1) * LABFM_NUM_OPS + d];
-            }
-            const double Wq = hx[deg - bb] * hy[bb];
-#pragma unroll
-            for (int d = 0; d < LABFM_NUM_OPS; ++d) {
-              wd[d] = fma(Wq, r0[d], wd[d]);
-              pin(wd[d]);
-            }
-#pragma unroll
-            for (int d = 0; d < LABFM_NUM_OPS; ++d) r0[d] = r1[d];
-          }
-        }
-#pragma unroll
-        for (int d = 0; d < LABFM_NUM_OPS; ++d) {
-          const int r = op_row(ga->rows, d);
-          if (r != kNoRow) {
-            ga->w[r * ga->nnz + e] = wd[d];
-            if (ga->w32) ga->w32[r * s32 + e] = static_cast<float>(wd[d]);
-          }
-          rs[d] += wd[d];
-        }
-#pragma unroll
-        for (int d = LABFM_OP_L; d <= LABFM_OP_XY; ++d) {
-          const double v32 = static_cast<double>(static_cast<float>(wd[d]));
-          mo[2 * (d - LABFM_OP_L)] += v32 * dx;
-          mo[2 * (d - LABFM_OP_L) + 1] += v32 * dy;
-        }
-        f0 += (1.0 - cos(kf * dx) * cos(kf * dy)) * wd[LABFM_OP_HYP];
-      }
-    }
-    if (k0 < K) {
-      const int k = k0 + (lane & 31);
-      const int og = lane >> 5;
-      int pbase = 0;
-      asm volatile("" : "+v"(pbase));
-      if (k < K) {
-        double dx, dy, hx[M + 1], hy[M + 1];
-        basis_of(k, dx, dy, hx, hy);
-        const long long e = e0 + k;
-        constexpr int H3 = LABFM_NUM_OPS / 2;
-        static_assert(LABFM_OP_L == 2 && LABFM_OP_XX == 3 && LABFM_OP_XY == 4 &&
-                          LABFM_OP_HYP == 5,
-                      "operator groups of a half pass: (x, y, L), (xx, xy, hyp)");
-        const int ob = pbase + og * H3;  // this lane's operators in a Psi row
-        double wd[H3] = {0.0, 0.0, 0.0};
-        double r0[H3], r1[H3];
-#pragma unroll
-        for (int d = 0; d < H3; ++d) r0[d] = psi_t[ob + d];
-#pragma unroll
-        for (int deg = 1, q = 0; deg <= M; ++deg) {
-#pragma unroll
-          for (int bb = 0; bb <= deg; ++bb, ++q) {
-            if (q + 1 < N) {
-#pragma unroll
-              for (int d = 0; d < H3; ++d) r1[d] = psi_t[ob + (q + 1) * LABFM_NUM_OPS + d];
-            }
-            const double Wq = hx[deg - bb] * hy[bb];
-#pragma unroll
-            for (int d = 0; d < H3; ++d) {
-              wd[d] = fma(Wq, r0[d], wd[d]);
-              pin(wd[d]);
-            }
-#pragma unroll
-            for (int d = 0; d < H3; ++d) r0[d] = r1[d];
-          }
-        }
-#pragma unroll
-        for (int d = 0; d < H3; ++d) {
-          const int r = op_row(ga->rows, og * H3 + d);
-          if (r != kNoRow) {
-            ga->w[r * ga->nnz + e] = wd[d];
-            if (ga->w32) ga->w32[r * s32 + e] = static_cast<float>(wd[d]);
-          }
-          // each sum takes this lane's value for its own operators only
-          rs[d] += og ? 0.0 : wd[d];
-          rs[H3 + d] += og ? wd[d] : 0.0;
-        }
-        // L is the first group's third operator, xx and xy the second's
-        // first two, hyp its third
-        const double vl = og ? 0.0 : static_cast<double>(static_cast<float>(wd[2]));
-        const double vxx = og ? static_cast<double>(static_cast<float>(wd[0])) : 0.0;
-        const double vxy = og ? static_cast<double>(static_cast<float>(wd[1])) : 0.0;
-        mo[0] += vl * dx;
-        mo[1] += vl * dy;
-        mo[2] += vxx * dx;
-        mo[3] += vxx * dy;
-        mo[4] += vxy * dx;
-        mo[5] += vxy * dy;
-        // one cosine per lane: the first half takes x, the second y and
-        // the x factor from its partner (lanes l and l + 32 share neighbour
-        // k and are active together); the second half holds hyp
-        const double cf = cos(kf * (og ? dy : dx));
-        const double cx = __shfl_xor(cf, 32);
-        f0 += og ? (1.0 - cx * cf) * wd[2] : 0.0;
-      }
-    }
-    f0 = group_sum<64>(f0);
-    // the row sums and first moments are reduced only when they are asked for
-    if (ga->rowsum) {
-#pragma unroll
-      for (int d = 0; d < LABFM_NUM_OPS; ++d) rs[d] = group_sum<64>(rs[d]);
-    }
-    if (ga->mom32) {
-#pragma unroll
-      for (int q = 0; q < kMoments; ++q) mo[q] = group_sum<64>(mo[q]);
-    }
-    if (lane == 0) {
-      if (ga->mom32)
-#pragma unroll
-        for (int q = 0; q < kMoments; ++q) ga->mom32[q * (long long)ga->n + i] = static_cast<float>(mo[q]);
-      const bool bad = !isfinite(f0) || f0 == 0.0;
-      ga->kappa[i] = bad ? 0.0 : 2.0 / (3.0 * f0);
-      if (st == LABFM_NODE_OK && bad) st = LABFM_NODE_BAD_FILTER;
-      ga->status[i] = static_cast<int8_t>(st);
-      if (ga->rowsum)
-#pragma unroll
-        for (int d = 0; d < LABFM_NUM_OPS; ++d)
-          if (op_row(ga->rows, d) != kNoRow) ga->rowsum[op_row(ga->rows, d) * (long long)ga->n + i] = rs[d];
-    }
+    node_weights<M, LABFM_NUM_OPS>(i, e0, K, st, psi_t);
   } else {
     if constexpr (kSolve) {
       if (lane == 0) sv.status[k_] = LABFM_NODE_SINGULAR;
       return;
     }
-    KernargBuildArgs* ga = build_args_again();
-    const long long s32 = w32_stride(ga->nnz);
-    for (int k = lane; k < K; k += 64)
-      for (int d = 0; d < LABFM_NUM_OPS; ++d) {
-        const int r = op_row(ga->rows, d);
-        if (r == kNoRow) continue;
-        ga->w[r * ga->nnz + e0 + k] = 0.0;
-        if (ga->w32) ga->w32[r * s32 + e0 + k] = 0.0f;
+    node_singular<LABFM_NUM_OPS>(i, e0, K);
+  }
+}
+
+// ---- several nodes per wavefront (orders 1 to 6) ------------------------------
+//
+// A wavefront builds G nodes. The assembly and the weights take the nodes one
+// after another with all 64 lanes, as rows_node does; the LU and the back
+// substitution between them run for all G at once. Group g of GW = 64 / G
+// lanes holds node g, row s GW + l in slot s (of SL) of the group's lane l. At
+// column c each group finds its pivot (exact comparison, lowest row on ties,
+// as in rows_node); the pivot's lane writes its row to LDS and the group's
+// lanes read it back, one broadcast read of two values serving G nodes and SL
+// rows per lane. In rows_node the row goes through scalar registers, two
+// v_readlane per value and node, and the updates run on n of 64 lanes: with
+// n = 27 that kernel issued instructions all of its time. Here a value costs
+// SL / G FMAs and no other vector instruction, and the pivot search is shared
+// by G nodes. The operations on each node are those of rows_node, in its
+// order: the outputs are the same bits. 65,536 nodes, one node per wavefront
+// -> this: m = 4 376 -> 234 us, m = 5 597 -> 421 us, m = 6 804 -> 598 us (each
+// with the sorting of the nodes by order, about 30 us).
+// Orders 7 to 10 stay with rows_node: two groups of 32 lanes with two rows of
+// 41 or 50 values a lane fill the registers of two wavefronts per SIMD and
+// write each pivot row from two slots, 1,330 against 1,298 us at m = 7 and
+// 1,800 against 1,656 us at m = 8; at orders 9 and 10 the rows alone exceed
+// the registers.
+
+constexpr int kGroupMax = 6;  // highest order built this way
+// Fewest nodes of an order built this way: below two rounds of one-node
+// wavefronts (4,096 in flight each) those finish sooner (kernel and sorting,
+// m = 4, 5, 6 at 2,025 nodes: 61, 70, 81 us against 71, 86, 106; at 6,400: 86,
+// 110, 138 against 81, 106, 135, but 88 against 100 us for 5,890 nodes of order
+// 6 among others; at 8,281: 95, 127, 161 against 86, 117, 154).
+constexpr int kGroupMin = 8192;
+
+template <int M, int NOPS>
+struct GroupShape {
+  static constexpr int N = RowShape<M>::N, NB = RowShape<M>::NB;
+  // nodes per wavefront: four, but two for the three operators of order 6
+  // (27 rows in groups of 32 lanes: twice the wavefronts, four per SIMD;
+  // stencil optimisation of 16,384 nodes 23.1 -> 21.7 ms)
+  static constexpr int G = (M == 6 && NOPS == 3) ? 2 : 4;
+  static constexpr int GW = 64 / G;                 // lanes per node
+  static constexpr int SL = (N + GW - 1) / GW;      // rows per lane
+  // columns of a strip and its row stride (doubles, odd): half tiles at four
+  // nodes of order 6, so that three wavefronts' LDS fits each SIMD's share
+  static constexpr int SC = (M == 6 && G == 4) ? 8 : 16;
+  static constexpr int SS = SC + 1;
+};
+
+// LDS of a wavefront: the basis tables of one node, then the G nodes' strips,
+// then their pivot rows and solutions.
+template <int M, int NOPS>
+struct alignas(16) GroupSmem {
+  using S = GroupShape<M, NOPS>;
+  static constexpr int RC = (S::N + NOPS + 1) & ~1;  // row length, even
+  static constexpr int kRow = RC + 2;                // pivot row stride
+  static constexpr int kPsi = S::N * psi_stride<NOPS>();
+  static constexpr int kTable = RowShape<M>::kTable;
+  static constexpr int kStrips = S::G * S::N * S::SS;
+  static constexpr int kSolve = S::G * (kRow + kPsi);
+  double buf[kTable > kStrips ? (kTable > kSolve ? kTable : kSolve)
+                              : (kStrips > kSolve ? kStrips : kSolve)];
+};
+
+// Orders LDS accesses between the lanes of one wavefront: the hardware keeps
+// a wavefront's LDS operations in order, so only the compiler is held.
+__device__ __forceinline__ void wave_lds_fence() {
+  __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront", "local");
+  __builtin_amdgcn_wave_barrier();
+  __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront", "local");
+}
+
+// Largest 32-bit key of each group of GW = 16 or 32 lanes, in all its lanes.
+template <int GW>
+__device__ __forceinline__ unsigned group_max_u32(unsigned v) {
+  static_assert(GW == 16 || GW == 32, "groups of one or two rows of lanes");
+  v = max(v, static_cast<unsigned>(__builtin_amdgcn_update_dpp(0, static_cast<int>(v), 0xB1, 0xF,
+                                                               0xF, false)));  // quad [1,0,3,2]
+  v = max(v, static_cast<unsigned>(__builtin_amdgcn_update_dpp(0, static_cast<int>(v), 0x4E, 0xF,
+                                                               0xF, false)));  // quad [2,3,0,1]
+  v = max(v, static_cast<unsigned>(__builtin_amdgcn_update_dpp(0, static_cast<int>(v), 0x141, 0xF,
+                                                               0xF, false)));  // half-row mirror
+  v = max(v, static_cast<unsigned>(__builtin_amdgcn_update_dpp(0, static_cast<int>(v), 0x140, 0xF,
+                                                               0xF, false)));  // row mirror
+  if constexpr (GW == 32) {
+    const auto rows = __builtin_amdgcn_permlane16_swap(v, v, false, false);
+    v = max(static_cast<unsigned>(rows[0]), static_cast<unsigned>(rows[1]));
+  }
+  return v;
+}
+
+// Wavefronts per SIMD. The rows take 2 SL RC registers and, before them, the
+// accumulators of all G nodes 8 G NB^2: at m = 6 three wavefronts (168
+// registers, 43 spilled) took 598 us against 658 us at two (213, none).
+template <int M, int NOPS>
+constexpr int group_waves() {
+  return (M <= 4 || GroupShape<M, NOPS>::G == 2) ? 4 : 3;
+}
+
+// One wavefront's work: the builds of nodes list[G blockIdx.x ...] with NOPS
+// operators (six, or x, y and L), or, with kSolve, systems G blockIdx.x ... of
+// sv in place of the assembly and the weights.
+template <int M, int NOPS, bool kSolve>
+__device__ __forceinline__ void group_nodes(BuildArgs g, const int* __restrict__ list, int count,
+                                            SolveArgs sv) {
+  using S = GroupShape<M, NOPS>;
+  using Smem = GroupSmem<M, NOPS>;
+  constexpr int N = S::N, NB = S::NB, G = S::G, GW = S::GW, SL = S::SL, SS = S::SS;
+  constexpr int SC = S::SC;
+  constexpr int RC = Smem::RC, PST = psi_stride<NOPS>();
+  __shared__ Smem sm;
+  const int lane = threadIdx.x;
+  const int grp = lane / GW, gl = lane % GW;
+  const int base = blockIdx.x * G;
+  // node (or system) q of this wavefront, -1 past the end or left out
+  auto node_of = [&](int q) {
+    const int k = base + q;
+    if (k >= count) return -1;
+    if (kSolve) return k;
+    const int i = uniform(list[k]);
+    return (g.active && uniform(g.active[i]) == 0) ? -1 : i;
+  };
+  double a[SL][RC];
+  bool used[SL];  // rows past n never pivot and are never updated
+  int mycol[SL];
+  double myinv[SL];
+#pragma unroll
+  for (int s = 0; s < SL; ++s) {
+    used[s] = s * GW + gl >= N;
+    mycol[s] = used[s] ? N : -1;
+    myinv[s] = 0.0;
+  }
+  if constexpr (kSolve) {
+    constexpr int W = N + LABFM_NUM_OPS;
+    const bool have = base + grp < count;
+    const double* A = sv.sys + static_cast<long long>(have ? base + grp : base) * N * W;
+#pragma unroll
+    for (int s = 0; s < SL; ++s) {
+      const int r = used[s] ? 0 : s * GW + gl;
+#pragma unroll
+      for (int j = 0; j < RC; ++j) a[s][j] = (have && j < W) ? A[r * W + j] : 0.0;
+    }
+  } else {
+    int ea[NB], eb[NB];
+#pragma unroll
+    for (int P = 0; P < NB; ++P) {
+      const int p = P * 16 + (lane & 15);
+      if (p < N) {
+        exponents_of(p, ea[P], eb[P]);
+      } else {
+        ea[P] = -1;
+        eb[P] = -1;
       }
-    if (lane == 0) {
-      ga->kappa[i] = 0.0;
-      ga->status[i] = LABFM_NODE_SINGULAR;
-      if (ga->rowsum)
-        for (int d = 0; d < LABFM_NUM_OPS; ++d)
-          if (op_row(ga->rows, d) != kNoRow) ga->rowsum[op_row(ga->rows, d) * (long long)ga->n + i] = 0.0;
-      if (ga->mom32)
-        for (int q = 0; q < kMoments; ++q) ga->mom32[q * (long long)ga->n + i] = 0.0f;
+    }
+    double4_t acc[G][NB][NB];
+    bool any = false;
+#pragma unroll
+    for (int q = 0; q < G; ++q) {
+#pragma unroll
+      for (int P = 0; P < NB; ++P)
+#pragma unroll
+        for (int Q = 0; Q < NB; ++Q) acc[q][P][Q] = double4_t{0.0, 0.0, 0.0, 0.0};
+      const int i = node_of(q);
+      if (i >= 0) {
+        any = true;
+        const int e0 = uniform(g.row_ptr[i]);
+        const int K = uniform(g.row_ptr[i + 1]) - e0;
+        assemble_tiles<M, NB, NB>(g, e0, K, g.x[i], g.y[i], 1.0 / g.h[i], ea, eb, 0, NB, sm.buf,
+                                  acc[q]);
+      }
+    }
+    if (!any) return;
+    // rows into registers, SC columns of all G nodes at a time; element v of
+    // lane l holds D[l/16 + 4v][l%16] of its 16x16 tile
+    double* strip = sm.buf;
+#pragma unroll
+    for (int Q = 0; Q < NB; ++Q) {
+#pragma unroll
+      for (int j0 = 0; j0 < 16; j0 += SC) {
+        if (Q * 16 + j0 < N) {
+          const int jl = (lane & 15) - j0;
+#pragma unroll
+          for (int q = 0; q < G; ++q)
+#pragma unroll
+            for (int P = 0; P < NB; ++P)
+#pragma unroll
+              for (int v = 0; v < 4; ++v) {
+                const int r = P * 16 + (lane >> 4) + 4 * v;
+                if (r < N && jl >= 0 && jl < SC) strip[(q * N + r) * SS + jl] = acc[q][P][Q][v];
+              }
+          wave_lds_fence();
+#pragma unroll
+          for (int s = 0; s < SL; ++s) {
+            const int r = used[s] ? 0 : s * GW + gl;
+#pragma unroll
+            for (int j = 0; j < SC; ++j)
+              if (Q * 16 + j0 + j < N) a[s][Q * 16 + j0 + j] = strip[(grp * N + r) * SS + j];
+          }
+          wave_lds_fence();
+        }
+      }
+    }
+    const int k = base + grp < count ? base + grp : base;
+    const double h = g.h[list[k]];
+#pragma unroll
+    for (int s = 0; s < SL; ++s) {
+      int ra = 0, rb = 0;
+      if (!used[s]) exponents_of(s * GW + gl, ra, rb);
+      double c[LABFM_NUM_OPS];
+      rhs_row(ra, rb, M, h, c);
+#pragma unroll
+      for (int d = 0; d < NOPS; ++d) a[s][N + d] = c[d];
+      if (RC > N + NOPS) a[s][RC - 1] = 0.0;
     }
   }
+
+  // ---- LU with partial pivoting, rows in place --------------------------------
+  // A zero or non-finite pivot marks the group's node singular; its later
+  // columns run on (no result of theirs is used).
+  double* prow = sm.buf + grp * Smem::kRow;
+  double* psi = sm.buf + G * Smem::kRow;
+  int sing = 0;
+#pragma unroll
+  for (int c = 0; c < N; ++c) {
+    // the lane's largest |a| of an unused row, as a bit pattern; the lower
+    // slot on ties
+    unsigned long long key = 0;
+    int ps = 0;
+    bool cand = false;
+#pragma unroll
+    for (int s = 0; s < SL; ++s) {
+      const unsigned long long bits =
+          static_cast<unsigned long long>(__double_as_longlong(fabs(a[s][c])));
+      const bool take = !used[s] && (!cand || bits > key);
+      key = take ? bits : key;
+      ps = take ? s : ps;
+      cand = cand || !used[s];
+    }
+    const unsigned hi = cand ? static_cast<unsigned>(key >> 32) : 0u;
+    const unsigned khi = group_max_u32<GW>(hi);
+    bool top = cand && hi == khi;
+    if (__builtin_popcountll(__builtin_amdgcn_ballot_w64(top)) != G) {
+      // equal high words in some group: compare the low words, then the rows
+      const unsigned lo = top ? static_cast<unsigned>(key) : 0u;
+      const unsigned klo = group_max_u32<GW>(lo);
+      top = top && lo == klo;
+      const unsigned up = top ? static_cast<unsigned>(SL * GW - (ps * GW + gl)) : 0u;
+      top = group_max_u32<GW>(up) == up && top;
+    }
+#pragma unroll
+    for (int s = 0; s < SL; ++s) {
+      if (top && ps == s) {
+#pragma unroll
+        for (int j = c & ~1; j < RC; j += 2)
+          *reinterpret_cast<double2*>(&prow[j]) = make_double2(a[s][j], a[s][j + 1]);
+      }
+    }
+    wave_lds_fence();
+    const double ucc = prow[c];
+    // (fenced: a test left to the end would hold every u_cc until then)
+    sing |= (ucc == 0.0 || !isfinite(ucc)) ? 1 : 0;
+    asm volatile("" : "+v"(sing));
+    // 1 / u_cc: hardware reciprocal and one Newton step
+    double inv = __builtin_amdgcn_rcp(ucc);
+    inv = fma(inv, fma(-ucc, inv, 1.0), inv);
+    double ln[SL];  // minus the multipliers (zero for used rows, +0.0)
+#pragma unroll
+    for (int s = 0; s < SL; ++s) {
+      const bool here = top && ps == s;
+      used[s] = used[s] || here;
+      mycol[s] = here ? c : mycol[s];
+      myinv[s] = here ? inv : myinv[s];
+      asm volatile("" : "+v"(mycol[s]));
+      ln[s] = used[s] ? 0.0 : a[s][c] * -inv;
+    }
+    // four values of the pivot row read, then their updates
+#pragma unroll
+    for (int j0 = (c + 1) & ~1; j0 < RC; j0 += 4) {
+      double2 u[2];
+#pragma unroll
+      for (int t = 0; t < 2; ++t)
+        if (j0 + 2 * t < RC) u[t] = *reinterpret_cast<const double2*>(&prow[j0 + 2 * t]);
+#pragma unroll
+      for (int t = 0; t < 2; ++t) {
+        const int j = j0 + 2 * t;
+#pragma unroll
+        for (int s = 0; s < SL; ++s) {
+          if (j < RC && j > c) {
+            a[s][j] = fma(ln[s], u[t].x, a[s][j]);
+            pin(a[s][j]);
+          }
+          if (j + 1 < RC && j + 1 > c) {
+            a[s][j + 1] = fma(ln[s], u[t].y, a[s][j + 1]);
+            pin(a[s][j + 1]);
+          }
+        }
+      }
+      __builtin_amdgcn_sched_barrier(0);
+    }
+    wave_lds_fence();
+  }
+
+  // ---- back substitution --------------------------------------------------------
+  // each row keeps its right-hand sides divided by its own pivot; column c's
+  // pivot row writes x_c into Psi and the group's other rows subtract
+  // (u_rc / u_qq) x_c
+  double* psi_g = psi + grp * Smem::kPsi;
+#pragma unroll
+  for (int s = 0; s < SL; ++s)
+#pragma unroll
+    for (int d = 0; d < NOPS; ++d) a[s][N + d] *= myinv[s];
+#pragma unroll
+  for (int c = N - 1; c >= 0; --c) {
+#pragma unroll
+    for (int s = 0; s < SL; ++s) {
+      if (mycol[s] == c) {
+#pragma unroll
+        for (int d = 0; d < NOPS; d += 2)
+          *reinterpret_cast<double2*>(&psi_g[c * PST + d]) =
+              make_double2(a[s][N + d], d + 1 < NOPS ? a[s][N + d + 1] : 0.0);
+      }
+    }
+    wave_lds_fence();
+    if (c > 0) {
+      double y[PST];
+#pragma unroll
+      for (int d = 0; d < PST; d += 2) {
+        const double2 v = *reinterpret_cast<const double2*>(&psi_g[c * PST + d]);
+        y[d] = v.x;
+        y[d + 1] = v.y;
+      }
+#pragma unroll
+      for (int s = 0; s < SL; ++s) {
+        const double coef = (mycol[s] < c) ? a[s][c] * myinv[s] : 0.0;
+#pragma unroll
+        for (int d = 0; d < NOPS; ++d) a[s][N + d] = fma(-coef, y[d], a[s][N + d]);
+      }
+    }
+    __builtin_amdgcn_sched_barrier(0);
+  }
+  const unsigned long long bad = __builtin_amdgcn_ballot_w64(sing != 0);
+  if constexpr (kSolve) {
+    if (base + grp < count) {
+      const long long k = base + grp;
+      if (!sing) {
+        for (int j = gl; j < N * NOPS; j += GW) sv.psi[k * N * NOPS + j] = psi_g[j];
+#pragma unroll
+        for (int s = 0; s < SL; ++s)
+          if (mycol[s] >= 0 && mycol[s] < N) sv.pivot_row[k * N + mycol[s]] = s * GW + gl;
+      }
+      if (gl == 0) sv.status[k] = sing ? LABFM_NODE_SINGULAR : LABFM_NODE_OK;
+    }
+  } else {
+#pragma unroll 1
+    for (int q = 0; q < G; ++q) {
+      const int i = node_of(q);
+      if (i < 0) continue;
+      const int e0 = uniform(g.row_ptr[i]);
+      const int K = uniform(g.row_ptr[i + 1]) - e0;
+      if ((bad >> (q * GW)) & 1) {
+        node_singular<NOPS>(i, e0, K);
+      } else {
+        node_weights<M, NOPS>(i, e0, K, K < N ? LABFM_NODE_FEW_NEIGHBOURS : LABFM_NODE_OK,
+                              psi + q * Smem::kPsi);
+      }
+    }
+  }
+}
+
+template <int M, int NOPS>
+__global__ void __launch_bounds__(64)
+__attribute__((amdgpu_waves_per_eu(group_waves<M, NOPS>())))
+build_group_kernel(BuildArgs g, const int* __restrict__ list, int count) {
+  group_nodes<M, NOPS, false>(g, list, count, SolveArgs{});
+}
+
+template <int M>
+__global__ void __launch_bounds__(64)
+__attribute__((amdgpu_waves_per_eu(group_waves<M, LABFM_NUM_OPS>())))
+group_solve_kernel(SolveArgs sv) {
+  group_nodes<M, LABFM_NUM_OPS, true>(BuildArgs{}, nullptr, sv.count, sv);
 }
 
 template <int M>
@@ -1864,10 +2293,30 @@ rows_solve_kernel(SolveArgs sv) {
   rows_node<M, true>(BuildArgs{}, nullptr, sv.count, sv);
 }
 
-template <int M>
+// Builds `count` nodes of order M with NOPS operators.
+template <int M, int NOPS>
 hipError_t launch_rows(const BuildArgs& g, const int* list, int count, hipStream_t st) {
   if (count <= 0) return hipSuccess;
+  if constexpr (M <= kGroupMax) {
+    if (count >= kGroupMin) {
+      hipLaunchKernelGGL((build_group_kernel<M, NOPS>),
+                         dim3(blocks_for(count, (GroupShape<M, NOPS>::G))), dim3(64), 0, st, g,
+                         list, count);
+      return hipGetLastError();
+    }
+  }
   hipLaunchKernelGGL(build_rows_kernel<M>, dim3(count), dim3(64), 0, st, g, list, count);
+  return hipGetLastError();
+}
+
+template <int M>
+hipError_t launch_solve(const SolveArgs& sv, hipStream_t st) {
+  if constexpr (M <= kGroupMax) {
+    hipLaunchKernelGGL(group_solve_kernel<M>, dim3(blocks_for(sv.count, (GroupShape<M, LABFM_NUM_OPS>::G))),
+                       dim3(64), 0, st, sv);
+  } else {
+    hipLaunchKernelGGL(rows_solve_kernel<M>, dim3(sv.count), dim3(64), 0, st, sv);
+  }
   return hipGetLastError();
 }
 
@@ -2317,16 +2766,16 @@ int build_weights_with(const double* x, const double* y, const double* h, const 
       });
       break;
     case LABFM_BUILD_ROWS: {
-      // orders 1..10: one wavefront per node with the rows in registers, one
-      // launch per order present; out-of-range orders (buckets of orders
-      // 15..11, and the bucket of orders <= 0) go to the workgroup kernel,
-      // which marks them unsupported
+      // orders 1..10: the rows in registers (several nodes per wavefront up to
+      // order 6, one above), one launch per order present; out-of-range orders
+      // (buckets of orders 15..11, and the bucket of orders <= 0) go to the
+      // workgroup kernel, which marks them unsupported
       for (int m = 1; m <= 10 && e == hipSuccess; ++m) {
         const int b = 15 - m;
         const int first = starts[b], count = starts[b + 1] - first;
         if (count <= 0) continue;
         e = with_rows_order(m, [&](auto M) {
-          return launch_rows<decltype(M)::value>(g, list + first, count, st);
+          return launch_rows<decltype(M)::value, LABFM_NUM_OPS>(g, list + first, count, st);
         });
       }
       if (e == hipSuccess && starts[5] > starts[0])
@@ -2475,8 +2924,7 @@ extern "C" int labfm_solve_systems(int32_t m, const double* systems, int32_t cou
   sv.status = status;
   const hipStream_t st = as_stream(stream_);
   LABFM_HIP(with_rows_order(m, [&](auto mc) -> hipError_t {
-    hipLaunchKernelGGL(rows_solve_kernel<decltype(mc)::value>, dim3(count), dim3(64), 0, st, sv);
-    return hipGetLastError();
+    return launch_solve<decltype(mc)::value>(sv, st);
   }));
   return LABFM_OK;
 }
@@ -2679,7 +3127,7 @@ extern "C" int labfm_optimise_stencils(const double* x, const double* y, const d
       const int cnt = starts[b + 1] - starts[b];
       if (cnt <= 0) continue;
       const hipError_t e = with_rows_order(m, [&](auto M) {
-        return launch_rows<decltype(M)::value>(g, list + starts[b], cnt, st);
+        return launch_rows<decltype(M)::value, 3>(g, list + starts[b], cnt, st);
       });
       LABFM_HIP(e);
     }

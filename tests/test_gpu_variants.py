@@ -63,3 +63,61 @@ def test_alternating_tile_order(dev, side, prec_name):
     assert np.array_equal(out["tiled"], out["graph"])
     d = np.linalg.norm(out["tiled"] - out["untiled"]) / np.linalg.norm(out["untiled"])
     assert d <= 3e-14
+
+
+# one more and one less than the nodes of a wavefront, several wavefronts; 6 is
+# the last order with several systems per wavefront
+@pytest.mark.parametrize("m", [1, 2, 3, 4, 5, 6, 7])
+@pytest.mark.parametrize("count", [1, 3, 4, 5, 9])
+def test_systems_sharing_a_wavefront(dev, m, count):
+    """Systems solved side by side in a wavefront do not touch each other: the
+    last wavefront's missing systems, and a singular or non-finite system
+    among others. Diagonally dominant systems: numpy's solution to 1e-13 (n
+    eps times a condition number below 10)."""
+    from paper_2102_02019_amd import labfm
+
+    n = (m * m + 3 * m) // 2
+    rng = np.random.default_rng(10 * m + count)
+    S = rng.uniform(-1.0, 1.0, (count, n, n + 6))
+    S[:, :, :n] += 2.0 * n * np.eye(n)[rng.permutation(n)]
+    bad = {1: 0.0, 3: np.inf} if count > 3 else {}
+    for k, v in bad.items():
+        S[k, :, n // 2] = v
+    psi, piv, st = (t.cpu().numpy() for t in labfm.solve_systems(m, T(S, dev)))
+    for k in range(count):
+        if k in bad:
+            assert st[k] == labfm.NODE_SINGULAR
+            assert (psi[k] == 0.0).all() and (piv[k] == -1).all()
+            continue
+        assert st[k] == labfm.NODE_OK
+        assert sorted(piv[k]) == list(range(n))
+        ref = np.linalg.solve(S[k, :, :n], S[k, :, n:])
+        assert np.abs(psi[k] - ref).max() <= 1e-13 * np.abs(ref).max()
+
+
+@pytest.mark.parametrize("m", [1, 4, 5, 6])
+@pytest.mark.parametrize("n", [8191, 8192, 8193, 8195])
+def test_shared_wavefront_build_matches_workgroup_build(dev, m, n):
+    """Around the fewest nodes of an order that share wavefronts (8192), all
+    remainders of four but two: weights, kappa, row sums and statuses of the
+    default build against the workgroup-per-node build, whose pivots and
+    operation order differ: 1e-9 relative, above cond(M~) eps at these
+    orders."""
+    from paper_2102_02019_amd import labfm
+
+    nodes = inputs.jittered_lattice(93, seed=m, m=4, h_over_s={1: 1.2, 4: 1.55, 5: 1.9, 6: 2.2}[m])
+    nodes.m = np.full(nodes.n, 2, np.int8)
+    nodes.m[np.random.default_rng(n).permutation(nodes.n)[:n]] = m
+    x, y, h, s, mm = (T(getattr(nodes, k), dev) for k in ("x", "y", "h", "s", "m"))
+    rp, col = labfm.build_neighbours(x, y, h, nodes.box)
+    out = []
+    for mode in (labfm.BUILD_ROWS, labfm.BUILD_BLOCK):
+        labfm.set_build_config(mode)
+        try:
+            out.append(labfm.build_weights(x, y, h, s, mm, nodes.box, rp, col, rowsum=True))
+        finally:
+            labfm.set_build_config(0)
+    a, b = out
+    assert torch.equal(a.status, b.status)
+    for u, v in ((a.w, b.w), (a.kappa, b.kappa), (a.rowsum, b.rowsum)):
+        assert torch.linalg.norm(u - v) <= 1e-9 * torch.linalg.norm(v)

@@ -244,6 +244,18 @@ int labfm_build_neighbours(const double* x, const double* y, const double* h, in
                            void* stream);
 
 /*
+ * The fill of col alone, for a caller that sized col with a
+ * labfm_build_neighbours call returning LABFM_ERR_CAPACITY: the same x, y, h,
+ * n, row_ptr and workspace, unchanged since that call (the search's cell
+ * tables are in the workspace), its nnz_out, and col of at least nnz entries.
+ * Equivalent to calling labfm_build_neighbours again with that col, without
+ * repeating the search. Enqueued without synchronising.
+ */
+int labfm_fill_neighbours(const double* x, const double* y, const double* h, int32_t n,
+                          const int32_t* row_ptr, int32_t* col, int64_t capacity, int64_t nnz,
+                          void* workspace, size_t workspace_bytes, void* stream);
+
+/*
  * Weight construction (sections "LABFM" and "New ABFs"; eqs. disc_form,
  * lsys, w_abf, hermite; filter calibration of section "Spatial filtering").
  * For each node i of order m_i (1..10), with n = (m^2+3m)/2 moments:

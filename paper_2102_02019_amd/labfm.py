@@ -121,6 +121,8 @@ _SIGNATURES = {
     "labfm_build_neighbours": (ctypes.c_int, [_P, _P, _P, ctypes.c_int32, _Box, _P, _P,
                                               ctypes.c_int64, ctypes.POINTER(ctypes.c_int64), _P,
                                               ctypes.c_size_t, _P]),
+    "labfm_fill_neighbours": (ctypes.c_int, [_P, _P, _P, ctypes.c_int32, _P, _P, ctypes.c_int64,
+                                             ctypes.c_int64, _P, ctypes.c_size_t, _P]),
     "labfm_build_workspace_bytes": (ctypes.c_size_t, [ctypes.c_int32]),
     "labfm_optimise_workspace_bytes": (ctypes.c_size_t, [ctypes.c_int32, ctypes.c_int64]),
     "labfm_build_weights": (ctypes.c_int, [_P, _P, _P, _P, _P, ctypes.c_int32, _Box, _P, _P,
@@ -290,10 +292,8 @@ def build_neighbours(x: torch.Tensor, y: torch.Tensor, h: torch.Tensor, box):
     if code != ERR_CAPACITY:
         _check(code)
     col = torch.empty(max(1, nnz.value), dtype=torch.int32, device=x.device)
-    code = lib().labfm_build_neighbours(_ptr(x), _ptr(y), _ptr(h), n, _box(box), _ptr(row_ptr),
-                                        _ptr(col), col.numel(), ctypes.byref(nnz), _ptr(ws),
-                                        ws.numel(), _stream())
-    _check(code)
+    _check(lib().labfm_fill_neighbours(_ptr(x), _ptr(y), _ptr(h), n, _ptr(row_ptr), _ptr(col),
+                                       col.numel(), nnz.value, _ptr(ws), ws.numel(), _stream()))
     return row_ptr, col[: nnz.value]
 
 

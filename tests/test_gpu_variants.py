@@ -121,3 +121,51 @@ def test_shared_wavefront_build_matches_workgroup_build(dev, m, n):
     assert torch.equal(a.status, b.status)
     for u, v in ((a.w, b.w), (a.kappa, b.kappa), (a.rowsum, b.rowsum)):
         assert torch.linalg.norm(u - v) <= 1e-9 * torch.linalg.norm(v)
+
+
+def brute_rows(x, y, h, box):
+    """Row lengths and columns of the stencils from all pairs, in torch: every
+    product and sum rounded on its own, as the predicate demands."""
+    n = x.numel()
+    cols, lens = [], []
+
+    def wrap(d, L, on):
+        if not on:
+            return d
+        return torch.where(d > 0.5 * L, d - L, torch.where(d < -0.5 * L, d + L, d))
+
+    for i in torch.arange(n, device=x.device).split(max(1, 40_000_000 // n)):
+        dx = wrap(x[None, :] - x[i, None], box.Lx, box.periodic_x)
+        dy = wrap(y[None, :] - y[i, None], box.Ly, box.periodic_y)
+        r = 2.0 * h[i]
+        near = dx * dx + dy * dy <= (r * r)[:, None]
+        near[torch.arange(i.numel()), i] = False
+        lens.append(near.sum(1))
+        cols.append(near.nonzero()[:, 1])
+    return torch.cat(lens), torch.cat(cols)
+
+
+# sets around the sizes at which a workgroup's share changes and its last one
+# is partly filled; grids of one, two, three and five cells an axis; blocks of
+# more candidates than fit in LDS (768), within one cell and over several
+@pytest.mark.parametrize("n,cells,spread,px,py", [
+    (1, 4, 1.0, True, True), (15, 1, 1.0, False, False), (17, 2, 1.0, True, False),
+    (600, 3, 1.0, True, True), (700, 1, 1.0, False, False), (3000, 5, 1.0, False, True),
+    (5000, 12, 0.05, True, True), (5000, 12, 0.25, True, True), (4001, 2, 1.0, True, True),
+    (16383, 40, 1.0, True, True), (16385, 40, 1.0, False, False), (65535, 90, 1.0, True, True),
+    (65599, 90, 0.6, True, False)])
+def test_stencil_search_against_all_pairs(dev, n, cells, spread, px, py):
+    """Rows bit-exact and ascending; `spread` gathers the nodes into that
+    share of the box, across its corner."""
+    from paper_2102_02019_amd import labfm
+
+    rng = np.random.default_rng(n + cells)
+    box = inputs.Box(2.0, 1.5, px, py)
+    x = np.mod(rng.uniform(-0.5, 0.5, n) * spread * box.Lx + (0 if px else 1.0), box.Lx)
+    y = np.mod(rng.uniform(-0.5, 0.5, n) * spread * box.Ly + (0 if py else 0.75), box.Ly)
+    hmax = 0.2499 * min(box.Lx, box.Ly) if cells <= 2 else box.Ly / (2.01 * cells)
+    x, y, h = (T(a, dev) for a in (x, y, hmax * rng.uniform(0.3, 1.0, n)))
+    rp, col = labfm.build_neighbours(x, y, h, box)
+    lens, ref = brute_rows(x, y, h, box)
+    assert torch.equal(rp[1:].long() - rp[:-1].long(), lens) and int(rp[0]) == 0
+    assert torch.equal(col.long(), ref)

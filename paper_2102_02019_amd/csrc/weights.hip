@@ -465,9 +465,6 @@ struct BuildArgs {
   double* rowsum;
   int8_t* status;
   unsigned rows;  // output row of each operator (op_row)
-  // the rows kernel skips nodes whose flag is 0 (the stencil optimiser's
-  // passes); null: every node is built
-  const int8_t* active = nullptr;
 };
 
 constexpr int kBlock = 256;
@@ -1630,7 +1627,6 @@ __device__ __forceinline__ void rows_node(BuildArgs g, const int* __restrict__ l
   if (k_ >= count) return;
   const int lane = threadIdx.x;
   const int i = kSolve ? k_ : uniform(list ? list[k_] : k_);
-  if (!kSolve && g.active && uniform(g.active[i]) == 0) return;
   const int e0 = kSolve ? 0 : uniform(g.row_ptr[i]);
   const int K = kSolve ? N : uniform(g.row_ptr[i + 1]) - e0;
   const double xi = kSolve ? 0.0 : g.x[i], yi = kSolve ? 0.0 : g.y[i];
@@ -2010,14 +2006,8 @@ __device__ __forceinline__ void group_nodes(BuildArgs g, const int* __restrict__
   const int lane = threadIdx.x;
   const int grp = lane / GW, gl = lane % GW;
   const int base = blockIdx.x * G;
-  // node (or system) q of this wavefront, -1 past the end or left out
-  auto node_of = [&](int q) {
-    const int k = base + q;
-    if (k >= count) return -1;
-    if (kSolve) return k;
-    const int i = uniform(list[k]);
-    return (g.active && uniform(g.active[i]) == 0) ? -1 : i;
-  };
+  // node q of this wavefront, -1 past the end
+  auto node_of = [&](int q) { return base + q < count ? uniform(list[base + q]) : -1; };
   double a[SL][RC];
   bool used[SL];  // rows past n never pivot and are never updated
   int mycol[SL];
@@ -2051,7 +2041,6 @@ __device__ __forceinline__ void group_nodes(BuildArgs g, const int* __restrict__
       }
     }
     double4_t acc[G][NB][NB];
-    bool any = false;
 #pragma unroll
     for (int q = 0; q < G; ++q) {
 #pragma unroll
@@ -2060,14 +2049,12 @@ __device__ __forceinline__ void group_nodes(BuildArgs g, const int* __restrict__
         for (int Q = 0; Q < NB; ++Q) acc[q][P][Q] = double4_t{0.0, 0.0, 0.0, 0.0};
       const int i = node_of(q);
       if (i >= 0) {
-        any = true;
         const int e0 = uniform(g.row_ptr[i]);
         const int K = uniform(g.row_ptr[i + 1]) - e0;
         assemble_tiles<M, NB, NB>(g, e0, K, g.x[i], g.y[i], 1.0 / g.h[i], ea, eb, 0, NB, sm.buf,
                                   acc[q]);
       }
     }
-    if (!any) return;
     // rows into registers, SC columns of all G nodes at a time; element v of
     // lane l holds D[l/16 + 4v][l%16] of its 16x16 tile
     double* strip = sm.buf;
@@ -2347,7 +2334,8 @@ hipError_t with_rows_order(int m, Fn&& fn) {
 // psi = 0 and drop out of the system and the weights), then one wavefront per
 // node tests them. A node whose test fails, whose system is singular, or that
 // has taken max_iter + 1 shrinks keeps its last accepted scale and leaves the
-// loop; the host runs passes until no node is left.
+// loop; the others make up the next pass's list, so that the wavefronts of a
+// late pass are full; the host runs passes until no node is left.
 
 constexpr int kNk = 16;  // wavenumbers of the amplitude test
 
@@ -2365,39 +2353,65 @@ struct OptArgs {
   const int8_t* status;   // this pass's build status
   double* h;              // current scale
   int* k;                 // shrinks taken to reach it
-  int8_t* active;         // 1 while the node shrinks
-  int* remaining;         // nodes still shrinking
   double* h_out;          // last accepted scale (h0 until one is)
   int* iters;             // its shrink count
   double shrink, gain_max, res_coef;
   int max_iter;
 };
 
-// LDS of the test (one wavefront per node) for a chunk of neighbours: the
-// scaled monomial factors x^a/a! and y^b/b!, the sequences sin(k_q x),
-// sin(k_q y), cos(k_q x), cos(k_q y) for q = 1..16 (wavenumber innermost,
-// so the amplitude lanes of one operator read consecutive words; padded to
-// 17 against conflicts of the lanes writing them), and the weights.
-template <int MMAX>
+// LDS of the test (one wavefront per node) for 64 neighbours: the scaled
+// monomial factors x^a/a! and y^b/b! and the Laplacian weights.
+template <int M>
 struct AcceptSmem {
-  double tab[kChunk][2][MMAX + 1];
-  double trig[kChunk][4][kNk + 1];
-  double wv[3][kChunk];
+  // an odd row length: the lanes writing their rows meet no bank conflicts
+  static constexpr int kRow = 2 * (M + 1) + 1;
+  double tab[64][kRow];
+  double wl[64];
 };
 
 __global__ void __launch_bounds__(256)
-stencil_opt_init_kernel(const double* __restrict__ h0, const int8_t* __restrict__ order, int n,
-                        double* __restrict__ h, int* __restrict__ k, int8_t* __restrict__ active,
-                        double* __restrict__ h_out, int* __restrict__ iters,
-                        int* __restrict__ remaining, int count) {
+stencil_opt_init_kernel(const double* __restrict__ h0, int n, double* __restrict__ h,
+                        int* __restrict__ k,
+                        double* __restrict__ h_out, int* __restrict__ iters) {
   const int i = blockIdx.x * blockDim.x + threadIdx.x;
-  if (i == 0) *remaining = count;
   if (i >= n) return;
   h[i] = h0[i];
   k[i] = 0;
   h_out[i] = h0[i];
   iters[i] = 0;
-  active[i] = (order[i] >= 1 && order[i] <= kMaxOrder) ? 1 : 0;
+}
+
+// a's sum over lanes l and l ^ D in the lanes with bit D clear, b's in the
+// others.
+template <int D>
+__device__ __forceinline__ double halves_sum(double a, double b, int lane) {
+  if constexpr (D >= 16) {
+    // the swap leaves a's lower and b's lower lanes in one register, their
+    // upper lanes in the other
+    const long long ab = __double_as_longlong(a), bb = __double_as_longlong(b);
+    unsigned lo[2], hi[2];
+    if constexpr (D == 32) {
+      const auto l = __builtin_amdgcn_permlane32_swap(static_cast<unsigned>(ab),
+                                                      static_cast<unsigned>(bb), false, false);
+      const auto u = __builtin_amdgcn_permlane32_swap(static_cast<unsigned>(ab >> 32),
+                                                      static_cast<unsigned>(bb >> 32), false, false);
+      lo[0] = l[0], lo[1] = l[1], hi[0] = u[0], hi[1] = u[1];
+    } else {
+      const auto l = __builtin_amdgcn_permlane16_swap(static_cast<unsigned>(ab),
+                                                      static_cast<unsigned>(bb), false, false);
+      const auto u = __builtin_amdgcn_permlane16_swap(static_cast<unsigned>(ab >> 32),
+                                                      static_cast<unsigned>(bb >> 32), false, false);
+      lo[0] = l[0], lo[1] = l[1], hi[0] = u[0], hi[1] = u[1];
+    }
+    auto word = [&](int k) {
+      return __longlong_as_double(
+          static_cast<long long>((static_cast<unsigned long long>(hi[k]) << 32) | lo[k]));
+    };
+    return word(0) + word(1);
+  } else {
+    const double keep = (lane & D) ? b : a, send = (lane & D) ? a : b;
+    return keep + __shfl_xor(send, D, 64);
+  }
 }
 
 // The test of node i at its current scale h:
@@ -2410,17 +2424,29 @@ stencil_opt_init_kernel(const double* __restrict__ h0, const int8_t* __restrict_
 //      none NaN.
 // Passed, h becomes the node's accepted scale and is shrunk for the next
 // pass; failed (or singular, or past max_iter), the node leaves the loop.
-template <int MMAX>
+//
+// One wavefront per node, one lane per neighbour (64 at a time). A lane forms
+// its neighbour's sines and cosines of the 16 wavenumbers by recurrence in
+// registers and adds its share to 48 sums of its own, which a transposing
+// reduction over the wave (48 values to 3 a lane) finishes; the residual's
+// sums run over the neighbours in order, one lane per moment, from the
+// factors in LDS. When the sequences went through LDS to one lane per
+// (operator, wavenumber), a pass over 16,384 nodes of K = 97 took 155 us, all
+// of it issuing instructions; now 76 us.
+//
+// list: the nodes of order M still shrinking; goes_on[k] says whether list[k]
+// shrinks further.
+template <int M>
 __global__ void __launch_bounds__(64)
-stencil_accept_kernel(OptArgs a, const int* __restrict__ list, int count) {
-  __shared__ AcceptSmem<MMAX> sm;
+__attribute__((amdgpu_waves_per_eu(3)))
+stencil_accept_kernel(OptArgs a, const int* __restrict__ list, int count,
+                      int8_t* __restrict__ goes_on) {
+  constexpr int N = moments_of(M), TW = M + 1;
+  __shared__ AcceptSmem<M> sm;
   const int kn = blockIdx.x;
   if (kn >= count) return;
   const int i = uniform(list[kn]);
-  if (uniform(a.active[i]) == 0) return;
   const int lane = threadIdx.x;
-  const int m = uniform(a.order[i]);
-  const int n = moments_of(m);
   const int e0 = uniform(a.row_ptr[i]);
   const int K = uniform(a.row_ptr[i + 1]) - e0;
   const int kcur = uniform(a.k[i]);
@@ -2430,78 +2456,103 @@ stencil_accept_kernel(OptArgs a, const int* __restrict__ list, int count) {
   const double k1 = M_PI / (s * kNk);
   // residual lanes: moments p = lane and lane + 64 (order 10 has 65)
   int pa0 = 0, pb0 = 0, pa1 = 0, pb1 = 0;
-  if (lane < n) exponents_of(lane, pa0, pb0);
-  if (lane + 64 < n) exponents_of(lane + 64, pa1, pb1);
+  if (lane < N) exponents_of(lane, pa0, pb0);
+  if (lane + 64 < N) exponents_of(lane + 64, pa1, pb1);
   double res0 = 0.0, res1 = 0.0;  // sum_j X~^p_j w^L_j (scaled monomials)
-  // amplitude lanes 0..47: operator aop (x, y, L), wavenumber aq
-  const int aop = lane >> 4, aq = lane & 15;
-  double amp = 0.0;
-  // chunk lanes: neighbour kk of the chunk, sequence t
-  const int kk = lane >> 2, t = lane & 3;
-  // the lane's neighbour one chunk ahead: coordinates and weight (t < 3)
-  double xn = 0.0, yn = 0.0, wn = 0.0;
-  if (kk < K) {
-    const int j = a.col[e0 + kk];
-    xn = a.x[j];
-    yn = a.y[j];
-    if (t < 3) wn = a.w[t * a.nnz + e0 + kk];
-  }
-  for (int k0 = 0; k0 < K; k0 += kChunk) {
-    const bool have = k0 + kk < K;
-    const double xj = xn, yj = yn, wj = wn;
-    if (k0 + kChunk + kk < K) {  // in flight while this chunk is tested
-      const int j = a.col[e0 + k0 + kChunk + kk];
+  double amp[3 * kNk];            // this lane's share of the sums, [operator][wavenumber]
+#pragma unroll
+  for (int q = 0; q < 3 * kNk; ++q) amp[q] = 0.0;
+  // the lane's neighbour, one round ahead
+  double xn = 0.0, yn = 0.0, wn[3] = {0.0, 0.0, 0.0};
+  auto fetch = [&](int k) {
+    if (k < K) {
+      const int j = a.col[e0 + k];
       xn = a.x[j];
       yn = a.y[j];
-      if (t < 3) wn = a.w[t * a.nnz + e0 + k0 + kChunk + kk];
+#pragma unroll
+      for (int d = 0; d < 3; ++d) wn[d] = a.w[d * a.nnz + e0 + k];
     }
+  };
+  fetch(lane);
+  for (int k0 = 0; k0 < K; k0 += 64) {
+    const bool have = k0 + lane < K;
+    const double xj = xn, yj = yn;
+    const double w0 = have ? wn[0] : 0.0, w1 = have ? wn[1] : 0.0, w2 = have ? wn[2] : 0.0;
+    fetch(k0 + 64 + lane);  // in flight while this round is tested
     double dx = 0.0, dy = 0.0;
     if (have) {
       dx = wrap_axis(xj - xi, a.box.Lx, px);
       dy = wrap_axis(yj - yi, a.box.Ly, py);
     }
-    if (t < 2) {
-      const double z = (t == 0 ? dx : dy) * hinv;
-      double v = 1.0;
-      sm.tab[kk][t][0] = have ? 1.0 : 0.0;
-#pragma unroll
-      for (int q = 1; q <= MMAX; ++q) {
-        v = v * z * (1.0 / static_cast<double>(q));  // z^q / q!
-        sm.tab[kk][t][q] = have ? v : 0.0;
-      }
-    }
-    if (t < 3) sm.wv[t][kk] = have ? wj : 0.0;
     {
-      // f(q+1) = 2 cos(theta) f(q) - f(q-1), from sin or cos of theta; the
-      // sine lanes (t = 0: x, 1: y) form sin and cos of their angle once and
-      // pass them to the cosine lanes (t = 2, 3) of the same neighbour
-      double sn = 0.0, cs = 0.0;
-      if (t < 2) sincos(k1 * (t == 0 ? dx : dy), &sn, &cs);
-      const int from = (lane & ~3) | (t & 1);
-      sn = __shfl(sn, from, 64);
-      cs = __shfl(cs, from, 64);
-      double f0 = (t < 2) ? 0.0 : 1.0, f1 = (t < 2) ? sn : cs;
-      sm.trig[kk][t][0] = f1;
+      const double zx = dx * hinv, zy = dy * hinv;
+      double vx = 1.0, vy = 1.0;
+      double* row = sm.tab[lane];
+      row[0] = 1.0;
+      row[TW] = 1.0;
 #pragma unroll
-      for (int q = 1; q < kNk; ++q) {
-        const double f2 = 2.0 * cs * f1 - f0;
-        f0 = f1;
-        f1 = f2;
-        sm.trig[kk][t][q] = f1;
+      for (int q = 1; q <= M; ++q) {
+        vx = vx * zx * (1.0 / static_cast<double>(q));  // z^q / q!
+        vy = vy * zy * (1.0 / static_cast<double>(q));
+        row[q] = vx;
+        row[TW + q] = vy;
       }
+      sm.wl[lane] = w2;
+    }
+    // f(q+1) = 2 cos(theta) f(q) - f(q-1), from sin or cos of theta
+    double sx1, cx1, sy1, cy1;
+    sincos(k1 * dx, &sx1, &cx1);
+    sincos(k1 * dy, &sy1, &cy1);
+    const double tx = 2.0 * cx1, ty = 2.0 * cy1;
+    double sx0 = 0.0, cx0 = 1.0, sy0 = 0.0, cy0 = 1.0;
+#pragma unroll
+    for (int q = 0; q < kNk; ++q) {
+      amp[q] += w0 * sx1;
+      amp[kNk + q] += w1 * sy1;
+      amp[2 * kNk + q] += w2 * (0.5 - 0.5 * cx1 * cy1);
+      const double sx2 = tx * sx1 - sx0, cx2 = tx * cx1 - cx0;
+      const double sy2 = ty * sy1 - sy0, cy2 = ty * cy1 - cy0;
+      sx0 = sx1;
+      sx1 = sx2;
+      cx0 = cx1;
+      cx1 = cx2;
+      sy0 = sy1;
+      sy1 = sy2;
+      cy0 = cy1;
+      cy1 = cy2;
     }
     lds_barrier();
-    for (int c = 0; c < kChunk; ++c) {
-      const double wl = sm.wv[2][c];
-      if (lane < n) res0 += (sm.tab[c][0][pa0] * sm.tab[c][1][pb0]) * wl;
-      if (lane + 64 < n) res1 += (sm.tab[c][0][pa1] * sm.tab[c][1][pb1]) * wl;
-      if (lane < 3 * kNk) {
-        const double f = (aop == 2) ? 0.5 - 0.5 * sm.trig[c][2][aq] * sm.trig[c][3][aq]
-                                    : sm.trig[c][aop][aq];
-        amp += sm.wv[aop][c] * f;
-      }
+    const int in = min(64, K - k0);
+#pragma unroll 8
+    for (int c = 0; c < in; ++c) {
+      const double wl = sm.wl[c];
+      if (lane < N) res0 += (sm.tab[c][pa0] * sm.tab[c][TW + pb0]) * wl;
+      if (lane + 64 < N) res1 += (sm.tab[c][pa1] * sm.tab[c][TW + pb1]) * wl;
     }
     lds_barrier();
+  }
+  // the 48 sums over the wave: at each halving the upper lanes take the upper
+  // half of the values; three are left to each group of four lanes
+#pragma unroll
+  for (int q = 0; q < 24; ++q) amp[q] = halves_sum<32>(amp[q], amp[q + 24], lane);
+#pragma unroll
+  for (int q = 0; q < 12; ++q) amp[q] = halves_sum<16>(amp[q], amp[q + 12], lane);
+#pragma unroll
+  for (int q = 0; q < 6; ++q) amp[q] = halves_sum<8>(amp[q], amp[q + 6], lane);
+#pragma unroll
+  for (int q = 0; q < 3; ++q) amp[q] = halves_sum<4>(amp[q], amp[q + 3], lane);
+  const int first = 24 * (lane >> 5) + 12 * ((lane >> 4) & 1) + 6 * ((lane >> 3) & 1) +
+                    3 * ((lane >> 2) & 1);
+  double av = -1.0;
+  bool bad = false;
+#pragma unroll
+  for (int q = 0; q < 3; ++q) {
+    const double v = group_sum<4>(amp[q]);
+    const int aop = (first + q) >> 4, aq = (first + q) & 15;
+    const double kq = k1 * static_cast<double>(aq + 1);
+    const double r = (aop == 2) ? v / (kq * kq) : v / kq;
+    bad = bad || !(r == r);
+    av = fmax(av, r);
   }
   // r_p = h^(a+b) res_p - C^L_p of the unscaled system
   auto rsq = [&](int pa, int pb, double res) {
@@ -2512,35 +2563,54 @@ stencil_accept_kernel(OptArgs a, const int* __restrict__ list, int count) {
     return r * r;
   };
   double sq = 0.0;
-  if (lane < n) sq += rsq(pa0, pb0, res0);
-  if (lane + 64 < n) sq += rsq(pa1, pb1, res1);
+  if (lane < N) sq += rsq(pa0, pb0, res0);
+  if (lane + 64 < N) sq += rsq(pa1, pb1, res1);
   const double ss = group_sum<64>(sq);
-  double av = -1.0;
-  bool bad = false;
-  if (lane < 3 * kNk) {
-    const double kq = k1 * static_cast<double>(aq + 1);
-    av = (aop == 2) ? amp / (kq * kq) : amp / kq;
-    bad = !(av == av);
-  }
   const bool nan_amp = __builtin_amdgcn_ballot_w64(bad) != 0;
 #pragma unroll
   for (int off = 32; off > 0; off >>= 1) av = fmax(av, __shfl_xor(av, off, 64));
-  double n4 = static_cast<double>(n);
+  double n4 = static_cast<double>(N);
   n4 = n4 * n4 * n4 * n4;
-  const double alpha0 = a.res_coef * 2.220446049250313e-16 * n4 / (h * static_cast<double>(m));
+  const double alpha0 = a.res_coef * 2.220446049250313e-16 * n4 / (h * static_cast<double>(M));
   const bool ok = a.status[i] != LABFM_NODE_SINGULAR && sqrt(ss) <= alpha0 && !nan_amp &&
                   av <= a.gain_max;
   if (lane == 0) {
-    if (!ok || kcur > a.max_iter) {
-      a.active[i] = 0;
-      atomicSub(a.remaining, 1);
-    } else {
+    const bool on = ok && kcur <= a.max_iter;
+    goes_on[kn] = on ? 1 : 0;
+    if (on) {
       a.h_out[i] = h;
       a.iters[i] = kcur;
       a.h[i] = h * a.shrink;
       a.k[i] = kcur + 1;
     }
   }
+}
+
+// The nodes of list that go on, in any order (a node's results are its own),
+// and their number: one atomic per workgroup (one per node, 16,384 on one
+// address, took 160 us).
+__global__ void __launch_bounds__(256)
+stencil_compact_kernel(const int* __restrict__ list, int count, const int8_t* __restrict__ goes_on,
+                       int* __restrict__ next, int* __restrict__ next_count) {
+  __shared__ int start[4];
+  __shared__ int base;
+  const int k = blockIdx.x * 256 + threadIdx.x;
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  const bool on = k < count && goes_on[k] != 0;
+  const unsigned long long mask = __builtin_amdgcn_ballot_w64(on);
+  if (lane == 0) start[wave] = __builtin_popcountll(mask);
+  __syncthreads();
+  if (threadIdx.x == 0) {
+    int sum = 0;
+    for (int w = 0; w < 4; ++w) {
+      const int c = start[w];
+      start[w] = sum;
+      sum += c;
+    }
+    base = sum > 0 ? atomicAdd(next_count, sum) : 0;
+  }
+  __syncthreads();
+  if (on) next[base + start[wave] + __builtin_popcountll(mask & ((1ull << lane) - 1ull))] = list[k];
 }
 
 // Work list: node indices grouped by order, highest order first (counting
@@ -3028,10 +3098,10 @@ extern "C" int labfm_tune_build(const double* x, const double* y, const double* 
   return LABFM_OK;
 }
 
-// Workspace of labfm_optimise_stencils: the node list, the x, y and L
-// weights of a pass, and the per-node state.
+// Workspace of labfm_optimise_stencils: the lists of this and the next pass's
+// nodes, the x, y and L weights of a pass, and the per-node state.
 struct OptLayout {
-  size_t list, w, h, kappa, k, iters, active, status, remaining, total;
+  size_t list, next, w, h, kappa, k, iters, goes_on, status, total;
   OptLayout(int32_t n, int64_t nnz) {
     size_t o = 0;
     auto take = [&](size_t bytes) {
@@ -3040,14 +3110,14 @@ struct OptLayout {
       return at;
     };
     list = take(build_work_bytes(n));
+    next = take(build_work_bytes(n));
     w = take(sizeof(double) * 3 * static_cast<size_t>(nnz));
     h = take(sizeof(double) * static_cast<size_t>(n));
     kappa = take(sizeof(double) * static_cast<size_t>(n));
     k = take(sizeof(int) * static_cast<size_t>(n));
     iters = take(sizeof(int) * static_cast<size_t>(n));
-    active = take(static_cast<size_t>(n));
+    goes_on = take(static_cast<size_t>(n));
     status = take(static_cast<size_t>(n));
-    remaining = take(sizeof(int));
     total = o;
   }
 };
@@ -3080,14 +3150,6 @@ extern "C" int labfm_optimise_stencils(const double* x, const double* y, const d
   int* list = work + kBuildWorkInts;
   int starts[17] = {0};
   if (int r = order_buckets(order_m, n, work, starts, st)) return r;
-  // bucket b holds order 15 - b: orders 10..1 are buckets 5..14
-  int mmax = 0;
-  for (int b = 5; b <= 14; ++b)
-    if (starts[b + 1] > starts[b]) {
-      mmax = 15 - b;
-      break;
-    }
-  const int first = starts[5], count = starts[15] - starts[5];
   OptArgs a{};
   a.x = x;
   a.y = y;
@@ -3101,46 +3163,54 @@ extern "C" int labfm_optimise_stencils(const double* x, const double* y, const d
   a.status = reinterpret_cast<int8_t*>(base + L.status);
   a.h = reinterpret_cast<double*>(base + L.h);
   a.k = reinterpret_cast<int*>(base + L.k);
-  a.active = reinterpret_cast<int8_t*>(base + L.active);
-  a.remaining = reinterpret_cast<int*>(base + L.remaining);
   a.h_out = h_out;
   a.iters = iters ? iters : reinterpret_cast<int*>(base + L.iters);
   a.shrink = p.shrink;
   a.gain_max = p.gain_max;
   a.res_coef = p.res_coef;
   a.max_iter = p.max_iter;
-  hipLaunchKernelGGL(stencil_opt_init_kernel, dim3(blocks_for(n, 256)), dim3(256), 0, st, h0,
-                     order_m, n, a.h, a.k, a.active, a.h_out, a.iters, a.remaining, count);
+  hipLaunchKernelGGL(stencil_opt_init_kernel, dim3(blocks_for(n, 256)), dim3(256), 0, st, h0, n,
+                     a.h, a.k, a.h_out, a.iters);
   LABFM_HIP(hipGetLastError());
-  if (count == 0) return LABFM_OK;
   // x, y and L weights of the nodes still shrinking, at their current scales
   BuildArgs g{x, y, a.h, s, order_m, n, box, row_ptr, col, nnz,
               reinterpret_cast<double*>(base + L.w), nullptr, nullptr,
               reinterpret_cast<double*>(base + L.kappa), nullptr,
               reinterpret_cast<int8_t*>(base + L.status),
               rows_of_mask((1u << LABFM_OP_X) | (1u << LABFM_OP_Y) | (1u << LABFM_OP_L))};
-  g.active = a.active;
+  // Two lists in turn, each with a part per order (order m's at starts[15 - m])
+  // and the parts' lengths in its first ints: a pass reads one and appends the
+  // nodes that go on to the other.
+  int* lists[2] = {work, reinterpret_cast<int*>(base + L.next)};
+  int8_t* goes_on = reinterpret_cast<int8_t*>(base + L.goes_on);
+  int left[kMaxOrder + 1] = {0};
+  for (int m = 1; m <= kMaxOrder; ++m) left[m] = starts[16 - m] - starts[15 - m];
   // a node takes at most max_iter + 2 tests (the last one rejected)
-  for (int pass = 0; pass <= p.max_iter + 1; ++pass) {
+  for (int pass = 0; pass <= p.max_iter + 2; ++pass) {
+    int all = 0;
+    for (int m = 1; m <= kMaxOrder; ++m) all += left[m];
+    if (all == 0) return LABFM_OK;
+    const int* from = lists[pass % 2] + kBuildWorkInts;
+    int* counts = lists[1 - pass % 2];
+    int* next = counts + kBuildWorkInts;
+    hipLaunchKernelGGL(zero_ints_kernel, dim3(1), dim3(64), 0, st, counts, kMaxOrder + 1);
     for (int m = 1; m <= kMaxOrder; ++m) {
-      const int b = 15 - m;
-      const int cnt = starts[b + 1] - starts[b];
-      if (cnt <= 0) continue;
-      const hipError_t e = with_rows_order(m, [&](auto M) {
-        return launch_rows<decltype(M)::value, 3>(g, list + starts[b], cnt, st);
+      if (left[m] == 0) continue;
+      const int at = starts[15 - m];
+      const hipError_t e = with_rows_order(m, [&](auto mc) {
+        constexpr int M = decltype(mc)::value;
+        const hipError_t r = launch_rows<M, 3>(g, from + at, left[m], st);
+        if (r != hipSuccess) return r;
+        hipLaunchKernelGGL(stencil_accept_kernel<M>, dim3(left[m]), dim3(64), 0, st, a, from + at,
+                           left[m], goes_on + at);
+        hipLaunchKernelGGL(stencil_compact_kernel, dim3(blocks_for(left[m], 256)), dim3(256), 0,
+                           st, from + at, left[m], goes_on + at, next + at, counts + m);
+        return hipGetLastError();
       });
       LABFM_HIP(e);
     }
-    const hipError_t e = with_mmax(mmax, [&](auto M) {
-      hipLaunchKernelGGL(stencil_accept_kernel<decltype(M)::value>, dim3(count), dim3(64), 0, st,
-                         a, list + first, count);
-      return hipGetLastError();
-    });
-    LABFM_HIP(e);
-    int left = 0;
-    LABFM_HIP(hipMemcpyAsync(&left, a.remaining, sizeof(int), hipMemcpyDeviceToHost, st));
+    LABFM_HIP(hipMemcpyAsync(left, counts, sizeof(left), hipMemcpyDeviceToHost, st));
     LABFM_HIP(hipStreamSynchronize(st));
-    if (left == 0) return LABFM_OK;
   }
   set_error("optimise_stencils: %s", "nodes still shrinking after max_iter + 2 passes");
   return LABFM_ERR_HIP;

@@ -169,3 +169,26 @@ def test_stencil_search_against_all_pairs(dev, n, cells, spread, px, py):
     lens, ref = brute_rows(x, y, h, box)
     assert torch.equal(rp[1:].long() - rp[:-1].long(), lens) and int(rp[0]) == 0
     assert torch.equal(col.long(), ref)
+
+
+@pytest.mark.parametrize("side,orders", [(9, (6,)), (17, (1, 2, 4, 11)), (16, (3, 6, 10))])
+def test_optimised_scales_do_not_depend_on_company(dev, side, orders):
+    """A node's optimised scale is its own: sets whose passes are cut down to
+    few nodes of several orders give each node what it gets when the others
+    are left out (order 0, which keeps h0)."""
+    from paper_2102_02019_amd import labfm
+
+    nodes = inputs.jittered_lattice(side, seed=side, m=4)
+    rng = np.random.default_rng(side)
+    m = rng.choice(np.array(orders, np.int8), nodes.n)
+    x, y, s = T(nodes.x, dev), T(nodes.y, dev), T(nodes.s, dev)
+    h0 = 1.9 * s
+    h, it = labfm.optimise_stencils(x, y, s, T(m, dev), nodes.box, h0=h0)
+    assert (it >= 0).all() and torch.equal(h[it == 0], h0[it == 0])
+    assert (it[T(m, dev) == 11] == 0).all()
+    some = rng.random(nodes.n) < 0.3
+    h1, it1 = labfm.optimise_stencils(x, y, s, T(np.where(some, m, 0).astype(np.int8), dev),
+                                      nodes.box, h0=h0)
+    some = T(some, dev)
+    assert torch.equal(h1[some], h[some]) and torch.equal(it1[some], it[some])
+    assert (it1[~some] == 0).all()

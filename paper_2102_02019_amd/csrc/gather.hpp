@@ -508,13 +508,19 @@ struct Tiles {
 // (Tiles::reverse): the weights that the last launch read at its end are
 // still in the 256 MB last-level cache when the next one begins with them.
 // Bitwise the same results. Measured per step of four stages and a filter on
-// 262,144 nodes, every launch upwards -> in turn: K = 90 float64 834 -> 805 us,
-// float32 weights 529 -> 497 us, K = 60 with walls 634 -> 594 us. Sets whose
+// 262,144 nodes, every launch upwards -> in turn: K = 90 float64 834 -> 797 us,
+// float32 weights 529 -> 491 us, K = 60 with walls 634 -> 591 us. Sets whose
 // weights fit the cache (65,536 nodes) or exceed it many times (4.2M) run the
 // same either way.
 template <int FL>
 __device__ __forceinline__ int tile_of_block(const Tiles& tl) {
-  const unsigned b = tl.reverse ? gridDim.x - 1 - blockIdx.x : blockIdx.x;
+  // eights of tiles in reverse, so that a tile stays on its XCD (every tile on
+  // another one made a step of 4,096 nodes, whose weights stay in the XCDs' L2
+  // caches, 9% slower); the last, incomplete eight stays last
+  const unsigned full = gridDim.x & ~(kXcds - 1);
+  const unsigned b = (tl.reverse && blockIdx.x < full)
+                         ? full - kXcds - (blockIdx.x & ~(kXcds - 1)) + (blockIdx.x & (kXcds - 1))
+                         : blockIdx.x;
   return static_cast<int>((FL & kXcdOrder) ? xcd_tile(b, gridDim.x) : b);
 }
 

@@ -15,10 +15,21 @@
 //     with P_4 = P_3 = qbar', P_2 = P_3 + Ybar_4, P_1 = P_2 + Ybar_3,
 //     qbar = P_1 + Ybar_2 + Ybar_1,
 // which uses the two-register structure of the scheme (a_ij = b_j for
-// j < i - 1). J_R^T is applied in two kernels: a forward gather at Y_i that
-// forms the twelve operator-sum adjoints g and the pointwise terms, then a
-// transposed gather of g. States are checkpointed every ckpt_every steps and
-// each segment is recomputed once before it is reversed.
+// j < i - 1). J_R^T at Y_i needs the forward operator sums at Y_i in a
+// pointwise part, which forms each node's operator-sum adjoints, and then a
+// transposed gather of these. The forward sums come from the stage launches
+// that recompute Y_2, Y_3, Y_4 (and one more at Y_4), which store them on the
+// way: no gather is repeated for them. Everything the pointwise part of stage
+// i - 1 reads besides is the node's own, so the transposed gather of stage i
+// does it when it has the node's Ybar_i; the filter's gather does that of
+// stage 4. A reversed step is then nine launches, all of them gathers.
+// States are checkpointed every ckpt_every steps and each segment is
+// recomputed once before it is reversed; the pass that makes the checkpoints
+// stops at the last of them.
+//
+// 65,536 nodes, m = 6, ten steps with checkpoints every five, forward run
+// included: 9.47 ms with a forward gather per stage, twelve operator-sum
+// adjoints per node in place of six values and single-edge loads; now 6.5 ms.
 #include <climits>
 
 #include "gather.hpp"
@@ -104,169 +115,251 @@ __global__ void tweights_kernel(const double* __restrict__ w, const int* __restr
 
 // ------------------------------------------------------------ adjoint kernels
 
-// Forward operator sums at Y and the pointwise part of J_R^T: with
-// Rbar = dtb P + dta Ynext (Ynext may be null), writes the twelve operator-sum
-// adjoints g[node][k] (l_x, l_y, u_x, u_y, Lu, u_xx, u_xy, v_x, v_y, Lv,
-// v_xx, v_xy; node-major, so the transposed gather reads a source node's
-// twelve values from one or two cache lines) and the pointwise adjoints
-// loc[f][node] of (ln rho, u, v).
-template <int LPN>
-__global__ void __launch_bounds__(256)
-adj_forward_kernel(const int* __restrict__ row_ptr, const int* __restrict__ col,
-                   const double* __restrict__ w, long long nnz, const double* __restrict__ Y,
-                   const double* __restrict__ P, const double* __restrict__ Ynext, double dtb,
-                   double dta, Flow fl, int n, double* __restrict__ g, double* __restrict__ loc) {
-  const int gid = blockIdx.x * blockDim.x + threadIdx.x;
-  const int node = gid / LPN;
-  const int sub = gid % LPN;
-  if (node >= n) return;
+// What the transposed gather reads of a source node i, kAdj values side by
+// side: the adjoints of its rates and the factors that turn them into those of
+// its operator sums, (rl, ru, rv, nu, u, v). From
+//   R_l = -(u l_x + v l_y) - (u_x + v_y)
+//   R_u = -(u u_x + v u_y) - c2 l_x + nu (Lu + (u_xx + v_xy)/3) + gx
+//   R_v = -(u v_x + v v_y) - c2 l_y + nu (4/3 Lv - v_xx/3 + u_xy/3) + gy
+// an edge of weights (a, b, c, d, f) (x, y, L, xx, xy) gives, with
+// t = a u + b v,
+//   ln rho:  -(rl t + c2 (a ru + b rv))
+//   u:       -(a rl + ru t) + nu (ru (c + d/3) + rv f/3)
+//   v:       -(b rl + rv t) + nu (rv (4 c - d)/3 + ru f/3).
+// (Twelve operator-sum adjoints a node, 96 bytes an edge, took 57 us for
+// 65,536 nodes of K = 60 with single-edge loads of the weights, eight 53 us
+// with pairs, these six 42 us.)
+constexpr int kAdj = 6;
+
+// The same for one edge or, with the row sums as weights, a node's own part.
+struct AdjSums {
+  double tl = 0.0, cl = 0.0, u = 0.0, v = 0.0;  // ln rho: -(tl + c2 cl)
+  __device__ __forceinline__ void add(double a, double b, double c, double d, double f,
+                                      const double* __restrict__ g) {
+    const double2* r = reinterpret_cast<const double2*>(g);
+    const double2 lu = r[0], vn = r[1], w = r[2];
+    constexpr double third = 1.0 / 3.0;
+    const double t = fma(a, w.x, b * w.y);
+    const double nru = vn.y * lu.y, nrv = vn.y * vn.x;
+    const double f3 = third * f;
+    tl = fma(lu.x, t, tl);
+    cl = fma(a, lu.y, fma(b, vn.x, cl));
+    u = fma(-a, lu.x, fma(-lu.y, t, u));
+    u = fma(fma(third, d, c), nru, fma(f3, nrv, u));
+    v = fma(-b, lu.x, fma(-vn.x, t, v));
+    v = fma(third * (4.0 * c - d), nrv, fma(f3, nru, v));
+  }
+};
+
+// The pointwise part at `node`: its record g from the stage's value Y and the
+// rates' adjoints r, and, with the stage's operator sums, the adjoints of
+// (ln rho, u, v) through the rates' own factors (d nu / d ln rho = -nu), loc.
+__device__ __forceinline__ void adj_point(int node, int n, const double* __restrict__ Y,
+                                          const double* __restrict__ sums, double rl, double ru,
+                                          double rv, const Flow& fl, double* __restrict__ g,
+                                          double* __restrict__ loc) {
   const long long n2 = 2 * static_cast<long long>(n);
   const double li = Y[node], ui = Y[n + node], vi = Y[n2 + node];
-  double acc[12];
-#pragma unroll
-  for (int k = 0; k < 12; ++k) acc[k] = 0.0;
-  for (int e = row_ptr[node] + sub; e < row_ptr[node + 1]; e += LPN) {
-    const int j = col[e];
-    const double dl = Y[j] - li, du = Y[n + j] - ui, dv = Y[n2 + j] - vi;
-    const double a = w[e], b = w[nnz + e], c = w[2 * nnz + e], d = w[3 * nnz + e],
-                 f = w[4 * nnz + e];
-    acc[0] = fma(a, dl, acc[0]);
-    acc[1] = fma(b, dl, acc[1]);
-    acc[2] = fma(a, du, acc[2]);
-    acc[3] = fma(b, du, acc[3]);
-    acc[4] = fma(c, du, acc[4]);
-    acc[5] = fma(d, du, acc[5]);
-    acc[6] = fma(f, du, acc[6]);
-    acc[7] = fma(a, dv, acc[7]);
-    acc[8] = fma(b, dv, acc[8]);
-    acc[9] = fma(c, dv, acc[9]);
-    acc[10] = fma(d, dv, acc[10]);
-    acc[11] = fma(f, dv, acc[11]);
-  }
-#pragma unroll
-  for (int k = 0; k < 12; ++k) acc[k] = group_sum<LPN>(acc[k]);
-  if (sub != 0) return;
-  const double lx = acc[0], ly = acc[1], ux = acc[2], uy = acc[3], uL = acc[4], uxx = acc[5];
-  const double uxy = acc[6], vx = acc[7], vy = acc[8], vL = acc[9], vxx = acc[10], vxy = acc[11];
-  double rl = dtb * P[node], ru = dtb * P[n + node], rv = dtb * P[n2 + node];
-  if (Ynext) {
-    rl += dta * Ynext[node];
-    ru += dta * Ynext[n + node];
-    rv += dta * Ynext[n2 + node];
-  }
+  const double2* s =
+      reinterpret_cast<const double2*>(sums + kStageSums * static_cast<long long>(node));
+  const double2 l = s[0], u = s[1], v = s[2], visc = s[3];
   const double nu = fl.mu / exp(li);
-  const double third = 1.0 / 3.0;
-  double* gn = g + 12LL * node;
-  // R_l = -(u l_x + v l_y) - (u_x + v_y)
-  // R_u = -(u u_x + v u_y) - c2 l_x + nu (Lu + (u_xx + v_xy)/3) + gx
-  // R_v = -(u v_x + v v_y) - c2 l_y + nu (4/3 Lv - v_xx/3 + u_xy/3) + gy
-  gn[0] = -ui * rl - fl.c2 * ru;
-  gn[1] = -vi * rl - fl.c2 * rv;
-  gn[2] = -rl - ui * ru;
-  gn[3] = -vi * ru;
-  gn[4] = nu * ru;
-  gn[5] = nu * ru * third;
-  gn[6] = nu * rv * third;
-  gn[7] = -ui * rv;
-  gn[8] = -rl - vi * rv;
-  gn[9] = 4.0 * third * nu * rv;
-  gn[10] = -nu * rv * third;
-  gn[11] = nu * ru * third;
-  // d nu / d ln rho = -nu
-  loc[node] = -nu * (ru * (uL + third * (uxx + vxy)) + rv * (vL + third * ((vL - vxx) + uxy)));
-  loc[n + node] = -rl * lx - ru * ux - rv * vx;
-  loc[n2 + node] = -rl * ly - ru * uy - rv * vy;
+  double2* gn = reinterpret_cast<double2*>(g + kAdj * static_cast<long long>(node));
+  gn[0] = make_double2(rl, ru);
+  gn[1] = make_double2(rv, nu);
+  gn[2] = make_double2(ui, vi);
+  loc[node] = -nu * (ru * visc.x + rv * visc.y);
+  loc[n + node] = -rl * l.x - ru * u.x - rv * v.x;
+  loc[n2 + node] = -rl * l.y - ru * u.y - rv * v.y;
 }
 
-// Transposed gather of g: Ybar_j = loc_j + sum_{i -> j} w^d_ij g_d(i) - S^d_j g_d(j),
-// then P_j += Pupd_j when Pupd is set (g node-major, g[i][d]).
-template <int LPN>
+// Which of the weights' arrays start on a pair of edges (16 bytes): all, with
+// an even nnz; those of even d, with an odd one; none need, where the weights
+// themselves start off it.
+enum { kAllPairs, kEvenPairs, kNoPairs };
+
+// Edges e, e + 1 (e even) of an array of `end` entries: one 16-byte load where
+// the array starts on a pair (the entry past the last one is then the next
+// array's first), two loads where it does not.
+template <bool kAligned>
+__device__ __forceinline__ double2 edge_pair(const double* __restrict__ p, long long e,
+                                             long long end) {
+  if constexpr (kAligned) {
+    return *reinterpret_cast<const double2*>(p + e);
+  } else {
+    return make_double2(p[e], e + 1 < end ? p[e + 1] : 0.0);
+  }
+}
+
+// Sources of the pair at e; the node itself for an edge outside e0 .. e1, whose
+// weights count as zero.
+__device__ __forceinline__ int2 pair_sources(const int* __restrict__ tsrc, int e, int e0, int e1,
+                                             int node) {
+  return make_int2(e >= e0 ? tsrc[e] : node, e + 1 < e1 ? tsrc[e + 1] : node);
+}
+
+// Where a stage's transposed gather leads: the pointwise part of the stage
+// before it (Y, sums, and its coefficients of P and Ybar), or, at stage 1
+// (Y null), the step's result qbar and, for the filter of the step before,
+// kappa qbar (kq, node-major in fours; null without the filter).
+struct AdjNext {
+  const double* Y;
+  const double* sums;
+  double dtb, dta;
+  double* g;
+  double* loc;
+  double* qbar;
+  double* kq;
+  const double* kappa;
+};
+
+__device__ __forceinline__ void store_kq(double* __restrict__ kq, int node, double k, double ql,
+                                         double qu, double qv) {
+  double2* d = reinterpret_cast<double2*>(kq + 4LL * node);
+  d[0] = make_double2(k * ql, k * qu);
+  d[1] = make_double2(k * qv, 0.0);
+}
+
+// Transposed gather: Ybar_j = loc_j + the sum over the edges i -> j less the
+// node's own part with the row sums, then P_j += Ynext_j when Ynext is set and what `nx` says. Bound by the
+// weights' stream (44 bytes an edge) with the 48-byte gathers of g beside it;
+// consecutive nodes go to one XCD, so that its L2 holds their sources.
+template <int LPN, int PAIRS>
 __global__ void __launch_bounds__(256)
 adj_transpose_kernel(const int* __restrict__ tptr, const int* __restrict__ tsrc,
                      const double* __restrict__ tw, long long nnz,
                      const double* __restrict__ rowsum, const double* __restrict__ g,
                      const double* __restrict__ loc, int n, double* __restrict__ Ybar,
-                     double* __restrict__ P, const double* __restrict__ Pupd) {
-  const int gid = blockIdx.x * blockDim.x + threadIdx.x;
+                     double* __restrict__ P, const double* __restrict__ Ynext, Flow fl,
+                     AdjNext nx) {
+  const int gid = static_cast<int>(xcd_tile(blockIdx.x, gridDim.x) * blockDim.x + threadIdx.x);
   const int node = gid / LPN;
   const int sub = gid % LPN;
   if (node >= n) return;
-  double sl = 0.0, su = 0.0, sv = 0.0;
-  for (int e = tptr[node] + sub; e < tptr[node + 1]; e += LPN) {
-    const int i = tsrc[e];
-    const double a = tw[e], b = tw[nnz + e], c = tw[2 * nnz + e], d = tw[3 * nnz + e],
-                 f = tw[4 * nnz + e];
-    const double* gi = g + 12LL * i;
-    sl = fma(a, gi[0], sl);
-    sl = fma(b, gi[1], sl);
-    su = fma(a, gi[2], su);
-    su = fma(b, gi[3], su);
-    su = fma(c, gi[4], su);
-    su = fma(d, gi[5], su);
-    su = fma(f, gi[6], su);
-    sv = fma(a, gi[7], sv);
-    sv = fma(b, gi[8], sv);
-    sv = fma(c, gi[9], sv);
-    sv = fma(d, gi[10], sv);
-    sv = fma(f, gi[11], sv);
+  AdjSums s;
+  const int e0 = tptr[node], e1 = tptr[node + 1];
+  for (int e = (e0 & ~1) + 2 * sub; e < e1; e += 2 * LPN) {
+    const int2 src = pair_sources(tsrc, e, e0, e1, node);
+    constexpr bool kEven = PAIRS != kNoPairs, kOdd = PAIRS == kAllPairs;
+    const double2 a = edge_pair<kEven>(tw, e, nnz), b = edge_pair<kOdd>(tw + nnz, e, nnz);
+    const double2 c = edge_pair<kEven>(tw + 2 * nnz, e, nnz);
+    const double2 d = edge_pair<kOdd>(tw + 3 * nnz, e, nnz);
+    const double2 f = edge_pair<kEven>(tw + 4 * nnz, e, nnz);
+    const bool in0 = e >= e0, in1 = e + 1 < e1;
+    s.add(in0 ? a.x : 0.0, in0 ? b.x : 0.0, in0 ? c.x : 0.0, in0 ? d.x : 0.0, in0 ? f.x : 0.0,
+          g + kAdj * static_cast<long long>(src.x));
+    s.add(in1 ? a.y : 0.0, in1 ? b.y : 0.0, in1 ? c.y : 0.0, in1 ? d.y : 0.0, in1 ? f.y : 0.0,
+          g + kAdj * static_cast<long long>(src.y));
   }
-  sl = group_sum<LPN>(sl);
-  su = group_sum<LPN>(su);
-  sv = group_sum<LPN>(sv);
+  const double sl = -(group_sum<LPN>(s.tl) + fl.c2 * group_sum<LPN>(s.cl));
+  const double su = group_sum<LPN>(s.u);
+  const double sv = group_sum<LPN>(s.v);
   if (sub != 0) return;
   const long long n2 = 2 * static_cast<long long>(n);
-  const double* S = rowsum;  // S[d * n + node]
-  const double* gj = g + 12LL * node;
-  const double dl = S[node] * gj[0] + S[n + node] * gj[1];
-  const double du = S[node] * gj[2] + S[n + node] * gj[3] + S[2 * n + node] * gj[4] +
-                    S[3 * n + node] * gj[5] + S[4 * n + node] * gj[6];
-  const double dv = S[node] * gj[7] + S[n + node] * gj[8] + S[2 * n + node] * gj[9] +
-                    S[3 * n + node] * gj[10] + S[4 * n + node] * gj[11];
-  Ybar[node] = loc[node] + (sl - dl);
-  Ybar[n + node] = loc[n + node] + (su - du);
-  Ybar[n2 + node] = loc[n2 + node] + (sv - dv);
-  if (Pupd) {
-    P[node] += Pupd[node];
-    P[n + node] += Pupd[n + node];
-    P[n2 + node] += Pupd[n2 + node];
+  const double* S = rowsum + node;  // S[d * n]
+  AdjSums own;
+  own.add(S[0], S[n], S[n2], S[n2 + n], S[2 * n2], g + kAdj * static_cast<long long>(node));
+  const double yl = loc[node] + (sl + (own.tl + fl.c2 * own.cl));
+  const double yu = loc[n + node] + (su - own.u);
+  const double yv = loc[n2 + node] + (sv - own.v);
+  double pl = P[node], pu = P[n + node], pv = P[n2 + node];
+  if (Ynext) {
+    pl += Ynext[node];
+    pu += Ynext[n + node];
+    pv += Ynext[n2 + node];
+  }
+  if (nx.Y) {
+    Ybar[node] = yl;
+    Ybar[n + node] = yu;
+    Ybar[n2 + node] = yv;
+    if (Ynext) {
+      P[node] = pl;
+      P[n + node] = pu;
+      P[n2 + node] = pv;
+    }
+    adj_point(node, n, nx.Y, nx.sums, nx.dtb * pl + nx.dta * yl, nx.dtb * pu + nx.dta * yu,
+              nx.dtb * pv + nx.dta * yv, fl, nx.g, nx.loc);
+  } else {
+    // qbar = P_1 + Ybar_2 + Ybar_1
+    const double ql = pl + yl, qu = pu + yu, qv = pv + yv;
+    nx.qbar[node] = ql;
+    nx.qbar[n + node] = qu;
+    nx.qbar[n2 + node] = qv;
+    if (nx.kq) store_kq(nx.kq, node, nx.kappa[node], ql, qu, qv);
   }
 }
 
-// Filter adjoint: out = qbar + A_hyp^T (kappa qbar), per field.
-template <int LPN>
+// Filter adjoint P = qbar + A_hyp^T (kappa qbar) per field, then the pointwise
+// part of stage 4 (its rates' adjoints are dtb P).
+template <int LPN, int PAIRS>
 __global__ void __launch_bounds__(256)
 adj_filter_kernel(const int* __restrict__ tptr, const int* __restrict__ tsrc,
-                  const double* __restrict__ twhyp, const double* __restrict__ Shyp,
-                  const double* __restrict__ kappa, const double* __restrict__ qbar, int n,
-                  double* __restrict__ out) {
-  const int gid = blockIdx.x * blockDim.x + threadIdx.x;
+                  const double* __restrict__ twhyp, long long nnz,
+                  const double* __restrict__ Shyp, const double* __restrict__ kq,
+                  const double* __restrict__ qbar, int n, double* __restrict__ P, Flow fl,
+                  AdjNext nx) {
+  const int gid = static_cast<int>(xcd_tile(blockIdx.x, gridDim.x) * blockDim.x + threadIdx.x);
   const int node = gid / LPN;
   const int sub = gid % LPN;
   if (node >= n) return;
   const long long n2 = 2 * static_cast<long long>(n);
   double sl = 0.0, su = 0.0, sv = 0.0;
-  for (int e = tptr[node] + sub; e < tptr[node + 1]; e += LPN) {
-    const int i = tsrc[e];
-    const double a = twhyp[e] * kappa[i];
-    sl = fma(a, qbar[i], sl);
-    su = fma(a, qbar[n + i], su);
-    sv = fma(a, qbar[n2 + i], sv);
+  const int e0 = tptr[node], e1 = tptr[node + 1];
+  for (int e = (e0 & ~1) + 2 * sub; e < e1; e += 2 * LPN) {
+    const int2 src = pair_sources(tsrc, e, e0, e1, node);
+    const double2 a = edge_pair<PAIRS == kAllPairs>(twhyp, e, nnz);
+#pragma unroll
+    for (int q = 0; q < 2; ++q) {
+      const bool in = q ? e + 1 < e1 : e >= e0;
+      const double w = in ? (q ? a.y : a.x) : 0.0;
+      const double2* ki = reinterpret_cast<const double2*>(kq + 4LL * (q ? src.y : src.x));
+      const double2 lu = ki[0];
+      sl = fma(w, lu.x, sl);
+      su = fma(w, lu.y, su);
+      sv = fma(w, ki[1].x, sv);
+    }
   }
   sl = group_sum<LPN>(sl);
   su = group_sum<LPN>(su);
   sv = group_sum<LPN>(sv);
   if (sub != 0) return;
-  const double ks = Shyp[node] * kappa[node];
-  out[node] = qbar[node] + (sl - ks * qbar[node]);
-  out[n + node] = qbar[n + node] + (su - ks * qbar[n + node]);
-  out[n2 + node] = qbar[n2 + node] + (sv - ks * qbar[n2 + node]);
+  const double s = Shyp[node];
+  const double2* kj = reinterpret_cast<const double2*>(kq + 4LL * node);
+  const double pl = qbar[node] + (sl - s * kj[0].x);
+  const double pu = qbar[n + node] + (su - s * kj[0].y);
+  const double pv = qbar[n2 + node] + (sv - s * kj[1].x);
+  P[node] = pl;
+  P[n + node] = pu;
+  P[n2 + node] = pv;
+  adj_point(node, n, nx.Y, nx.sums, nx.dtb * pl, nx.dtb * pu, nx.dtb * pv, fl, nx.g, nx.loc);
 }
 
-__global__ void add3_kernel(const double* __restrict__ a, const double* __restrict__ b,
-                            double* __restrict__ out, long long len) {
-  for (long long i = blockIdx.x * static_cast<long long>(blockDim.x) + threadIdx.x; i < len;
-       i += static_cast<long long>(gridDim.x) * blockDim.x)
-    out[i] = a[i] + b[i];
+// Without the filter: P = qbar and the pointwise part of stage 4.
+__global__ void __launch_bounds__(256)
+adj_start_kernel(const double* __restrict__ qbar, int n, double* __restrict__ P, Flow fl,
+                 AdjNext nx) {
+  const int node = blockIdx.x * blockDim.x + threadIdx.x;
+  if (node >= n) return;
+  const long long n2 = 2 * static_cast<long long>(n);
+  const double pl = qbar[node], pu = qbar[n + node], pv = qbar[n2 + node];
+  P[node] = pl;
+  P[n + node] = pu;
+  P[n2 + node] = pv;
+  adj_point(node, n, nx.Y, nx.sums, nx.dtb * pl, nx.dtb * pu, nx.dtb * pv, fl, nx.g, nx.loc);
+}
+
+// qbar = qbar_end, and kappa qbar when kq is set.
+__global__ void __launch_bounds__(256)
+adj_seed_kernel(const double* __restrict__ end, const double* __restrict__ kappa, int n,
+                double* __restrict__ qbar, double* __restrict__ kq) {
+  const int node = blockIdx.x * blockDim.x + threadIdx.x;
+  if (node >= n) return;
+  const long long n2 = 2 * static_cast<long long>(n);
+  const double ql = end[node], qu = end[n + node], qv = end[n2 + node];
+  qbar[node] = ql;
+  qbar[n + node] = qu;
+  qbar[n2 + node] = qv;
+  if (kq) store_kq(kq, node, kappa[node], ql, qu, qv);
 }
 
 long long ceil_div(long long a, long long b) { return (a + b - 1) / b; }
@@ -316,9 +409,12 @@ extern "C" int labfm_build_transpose(const labfm_operators* ops, int32_t* tptr, 
 extern "C" size_t labfm_adjoint_workspace_bytes(int32_t n, int32_t n_steps, int32_t ckpt_every) {
   if (n <= 0 || n_steps < 0 || ckpt_every <= 0) return 0;
   const long long nck = ceil_div(n_steps, ckpt_every) + 1;
-  // checkpoints, one recomputed segment, and 45 n doubles of registers
-  const long long doubles = 3LL * n * (nck + ckpt_every) + 45LL * n;
-  return static_cast<size_t>(doubles) * sizeof(double) + 256;
+  // checkpoints, one recomputed segment, and the registers of a reversed step:
+  // ten of 3 n doubles, the stages' sums, two sets of operator-sum adjoints
+  // with their pointwise terms, kappa qbar
+  const long long per_node = 10 * 3 + 4 * kStageSums + 2 * (kAdj + 3) + 4;
+  const long long doubles = 3LL * n * (nck + ckpt_every) + per_node * n;
+  return static_cast<size_t>(doubles) * sizeof(double) + 512;
 }
 
 extern "C" int labfm_rk_adjoint(const double* q0, const double* qbar_end, double* qbar_0,
@@ -345,8 +441,15 @@ extern "C" int labfm_rk_adjoint(const double* q0, const double* qbar_end, double
   const long long N3 = 3LL * n;
   const size_t b3 = sizeof(double) * N3;
   const long long nck = ceil_div(n_steps, ckpt_every) + 1;
-  double* ws = static_cast<double*>(workspace);
-  double* ck = ws;
+  // the records read with 16-byte loads first, on a 16-byte boundary
+  double* sums = reinterpret_cast<double*>((reinterpret_cast<uintptr_t>(workspace) + 15) &
+                                           ~static_cast<uintptr_t>(15));
+  double* g[2];
+  g[0] = sums + 4LL * kStageSums * n;
+  g[1] = g[0] + static_cast<long long>(kAdj) * n;
+  double* kq = g[1] + static_cast<long long>(kAdj) * n;
+  double* loc[2] = {kq + 4LL * n, kq + 4LL * n + N3};
+  double* ck = loc[1] + N3;
   double* seg = ck + nck * N3;
   double* Y2 = seg + static_cast<long long>(ckpt_every) * N3;
   double* Y3 = Y2 + N3;
@@ -358,8 +461,6 @@ extern "C" int labfm_rk_adjoint(const double* q0, const double* qbar_end, double
   double* P = qbar + N3;
   double* Ba = P + N3;
   double* Bb = Ba + N3;
-  double* g = Bb + N3;
-  double* loc = g + 12LL * n;
 
   const Flow fl{prm->c2, prm->mu, prm->gx, prm->gy};
   const double dt = prm->dt;
@@ -377,19 +478,30 @@ extern "C" int labfm_rk_adjoint(const double* q0, const double* qbar_end, double
   const LaunchCfg scfg = plan.stage_cfg;
   const long long nnz = ops->nnz;
   const unsigned grid = blocks_for(static_cast<long long>(n) * kAdjLpn, 256);
-  const unsigned gadd = static_cast<unsigned>(std::min<long long>(4096, ceil_div(N3, 256)));
+  const unsigned grid1 = blocks_for(n, 256);
+  const int pairs = reinterpret_cast<uintptr_t>(tr->tw) % 16 != 0
+                        ? kNoPairs
+                        : (nnz % 2 != 0 ? kEvenPairs : kAllPairs);
+  const auto transpose = pairs == kAllPairs    ? adj_transpose_kernel<kAdjLpn, kAllPairs>
+                         : pairs == kEvenPairs ? adj_transpose_kernel<kAdjLpn, kEvenPairs>
+                                               : adj_transpose_kernel<kAdjLpn, kNoPairs>;
+  const auto filter = pairs == kAllPairs ? adj_filter_kernel<kAdjLpn, kAllPairs>
+                                         : adj_filter_kernel<kAdjLpn, kNoPairs>;
 
-  // forward pass, keeping a checkpoint every ckpt_every steps
+  // forward pass up to the last checkpoint
+  const long long nseg = ceil_div(n_steps, ckpt_every);
   LABFM_HIP(hipMemcpyAsync(seg, q0, b3, hipMemcpyDeviceToDevice, st));
-  for (int k = 0; k < n_steps; ++k) {
-    if (k % ckpt_every == 0)
-      LABFM_HIP(hipMemcpyAsync(ck + (k / ckpt_every) * N3, seg, b3, hipMemcpyDeviceToDevice, st));
+  for (long long s = 0; s < nseg; ++s) {
+    LABFM_HIP(hipMemcpyAsync(ck + s * N3, seg, b3, hipMemcpyDeviceToDevice, st));
+    if (s + 1 == nseg) break;
     plan.Q = seg;
-    LABFM_HIP(enqueue_step<F64>(plan, st, nullptr));
+    for (int k = 0; k < ckpt_every; ++k) LABFM_HIP(enqueue_step<F64>(plan, st, nullptr));
   }
 
-  LABFM_HIP(hipMemcpyAsync(qbar, qbar_end, b3, hipMemcpyDeviceToDevice, st));
-  for (long long s = ceil_div(n_steps, ckpt_every) - 1; s >= 0; --s) {
+  hipLaunchKernelGGL(adj_seed_kernel, dim3(grid1), dim3(256), 0, st, qbar_end, ops->kappa, n, qbar,
+                     prm->filter ? kq : nullptr);
+  LABFM_LAUNCHED();
+  for (long long s = nseg - 1; s >= 0; --s) {
     const int k0 = static_cast<int>(s * ckpt_every);
     const int k1 = std::min(n_steps, k0 + ckpt_every);
     // recompute the segment's states q_k0 .. q_{k1-1}
@@ -402,39 +514,55 @@ extern "C" int labfm_rk_adjoint(const double* q0, const double* qbar_end, double
     }
     for (int k = k1 - 1; k >= k0; --k) {
       const double* q = seg + static_cast<long long>(k - k0) * N3;
-      // stage values Y2, Y3, Y4 of this step
-      LABFM_HIP(launch_stage<F64>(scfg, ops, ops->w, q, q, qs, Y2, dt * kA[0], dt * kB[0], fl, st));
-      LABFM_HIP(launch_stage<F64>(scfg, ops, ops->w, Y2, qs, qs, Y3, dt * kA[1], dt * kB[1], fl, st));
-      LABFM_HIP(launch_stage<F64>(scfg, ops, ops->w, Y3, qs, qs, Y4, dt * kA[2], dt * kB[2], fl, st));
+      // stage values Y2, Y3, Y4 of this step, and the operator sums at
+      // Y1 = q, Y2, Y3 and Y4
+      const double* Ys[4] = {q, Y2, Y3, Y4};
+      double* to[4] = {Y2, Y3, Y4, nullptr};
+      for (int i = 0; i < 4; ++i) {
+        Flow fs = fl;
+        fs.sums = sums + static_cast<long long>(i) * kStageSums * n;
+        LABFM_HIP(launch_stage<F64>(scfg, ops, ops->w, Ys[i], i == 0 ? q : qs, qs, to[i],
+                                    i < 3 ? dt * kA[i] : 0.0, dt * kB[i], fs, st, i & 1));
+      }
+      // the pointwise part of stage i, from the kernel that comes before its
+      // transposed gather
+      auto next = [&](int i) {
+        AdjNext nx{};
+        if (i >= 0) {
+          nx.Y = Ys[i];
+          nx.sums = sums + static_cast<long long>(i) * kStageSums * n;
+          nx.dtb = dt * kB[i];
+          nx.dta = i == 3 ? 0.0 : dt * kA[i];
+          nx.g = g[i % 2];
+          nx.loc = loc[i % 2];
+        } else {
+          nx.qbar = qbar;
+          nx.kq = prm->filter ? kq : nullptr;
+          nx.kappa = ops->kappa;
+        }
+        return nx;
+      };
       // filter adjoint: P = qbar + A_hyp^T (kappa qbar)
       if (prm->filter) {
-        hipLaunchKernelGGL(adj_filter_kernel<kAdjLpn>, dim3(grid), dim3(256), 0, st, tr->tptr,
-                           tr->tsrc, tr->tw + LABFM_OP_HYP * nnz, tr->rowsum + LABFM_OP_HYP * n,
-                           ops->kappa, qbar, n, P);
-        LABFM_LAUNCHED();
+        hipLaunchKernelGGL(filter, dim3(grid), dim3(256), 0, st, tr->tptr, tr->tsrc,
+                           tr->tw + LABFM_OP_HYP * nnz, nnz, tr->rowsum + LABFM_OP_HYP * n, kq,
+                           qbar, n, P, fl, next(3));
       } else {
-        LABFM_HIP(hipMemcpyAsync(P, qbar, b3, hipMemcpyDeviceToDevice, st));
+        hipLaunchKernelGGL(adj_start_kernel, dim3(grid1), dim3(256), 0, st, qbar, n, P, fl,
+                           next(3));
       }
-      // stages 4 .. 1 (index i = 3 .. 0): Ybar_4 -> Ba, Ybar_3 -> Bb,
-      // Ybar_2 -> Ba, Ybar_1 -> Bb. Stage index i reads P and Ybar_{i+1};
-      // its transposed gather then folds Ybar_{i+1} into P for stage i-1
-      // (P_2 = P_3 + Ybar_4, P_1 = P_2 + Ybar_3, and Ybar_2 last).
-      const double* Ys[4] = {q, Y2, Y3, Y4};
-      double* out[4] = {Bb, Ba, Bb, Ba};
-      for (int i = 3; i >= 0; --i) {
-        const double* ynext = (i == 3) ? nullptr : out[i + 1];
-        const double dta = (i == 3) ? 0.0 : dt * kA[i];
-        hipLaunchKernelGGL(adj_forward_kernel<kAdjLpn>, dim3(grid), dim3(256), 0, st,
-                           ops->row_ptr, ops->col, ops->w, nnz, Ys[i], P, ynext, dt * kB[i], dta,
-                           fl, n, g, loc);
-        LABFM_LAUNCHED();
-        hipLaunchKernelGGL(adj_transpose_kernel<kAdjLpn>, dim3(grid), dim3(256), 0, st, tr->tptr,
-                           tr->tsrc, tr->tw, nnz, tr->rowsum, g, loc, n, out[i], P, ynext);
-        LABFM_LAUNCHED();
-      }
-      // qbar = P_1 + Ybar_2 + Ybar_1 (P holds P_1 + Ybar_2 after the last fold)
-      hipLaunchKernelGGL(add3_kernel, dim3(gadd), dim3(256), 0, st, P, out[0], qbar, N3);
       LABFM_LAUNCHED();
+      // stages 4 .. 1 (index i = 3 .. 0): Ybar_4 -> Ba, Ybar_3 -> Bb,
+      // Ybar_2 -> Ba. Stage index i's transposed gather folds Ybar_{i+1} into
+      // P (P_2 = P_3 + Ybar_4, P_1 = P_2 + Ybar_3) before the pointwise part
+      // of stage i - 1; the last one leaves qbar = P_1 + Ybar_2 + Ybar_1.
+      double* out[4] = {nullptr, Ba, Bb, Ba};
+      for (int i = 3; i >= 0; --i) {
+        hipLaunchKernelGGL(transpose, dim3(grid), dim3(256), 0, st, tr->tptr, tr->tsrc, tr->tw, nnz,
+                           tr->rowsum, g[i % 2], loc[i % 2], n, out[i], P,
+                           i == 3 ? nullptr : out[i + 1], fl, next(i - 1));
+        LABFM_LAUNCHED();
+      }
     }
   }
   LABFM_HIP(hipMemcpyAsync(qbar_0, qbar, b3, hipMemcpyDeviceToDevice, st));

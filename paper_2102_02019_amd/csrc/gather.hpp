@@ -250,7 +250,12 @@ apply_kernel(const int* __restrict__ row_ptr, const int* __restrict__ col,
 
 struct Flow {
   double c2, mu, gx, gy;
+  // when set, a stage also stores what the adjoint needs of its operator sums:
+  // kStageSums values per node, node-major (l_x, l_y, u_x, u_y, v_x, v_y and
+  // the viscous terms of u and v without nu)
+  double* sums = nullptr;
 };
+constexpr int kStageSums = 8;
 
 // Wall normal of a node, or (0, 0) off the walls and when wn is null.
 __device__ __forceinline__ bool wall_node(const double* wn, int node, double& nx, double& ny) {
@@ -295,6 +300,13 @@ __device__ __forceinline__ void stage_update(int node, int n, double li, double 
   const double Vx = D[7], Vy = D[8], VL = D[9], Vxx = D[10], Vxy = D[11];
   const double nu = fl.mu / exp(li);
   const double third = 1.0 / 3.0;
+  if (fl.sums) {
+    double2* s = reinterpret_cast<double2*>(fl.sums + kStageSums * static_cast<long long>(node));
+    s[0] = make_double2(Lx, Ly);
+    s[1] = make_double2(Ux, Uy);
+    s[2] = make_double2(Vx, Vy);
+    s[3] = make_double2(UL + third * (Uxx + Vxy), VL + third * ((VL - Vxx) + Uxy));
+  }
   double rl = -(ui * Lx + vi * Ly) - (Ux + Vy);
   double ru = -(ui * Ux + vi * Uy) - fl.c2 * Lx + nu * (UL + third * (Uxx + Vxy)) + fl.gx;
   double rv = -(ui * Vx + vi * Vy) - fl.c2 * Ly + nu * (VL + third * ((VL - Vxx) + Uxy)) + fl.gy;

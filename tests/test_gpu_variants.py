@@ -192,3 +192,49 @@ def test_optimised_scales_do_not_depend_on_company(dev, side, orders):
     some = T(some, dev)
     assert torch.equal(h1[some], h[some]) and torch.equal(it1[some], it[some])
     assert (it1[~some] == 0).all()
+
+
+# an odd and an even number of stencil entries, and transposed weights that
+# start 8 bytes off a pair: the three ways the transposed gathers load edges;
+# steps that fill the last segment, leave it short, or make one segment
+@pytest.mark.parametrize("odd", [False, True])
+@pytest.mark.parametrize("steps,ckpt,filt", [(1, 3, True), (4, 2, True), (5, 2, False), (3, 7, True)])
+def test_adjoint_against_differences(dev, odd, steps, ckpt, filt):
+    """<J v, w> from central differences of the run (step 1e-6: truncation
+    about 1e-11, rounding 1e-9 of the product) against <v, J^T w>; the
+    misaligned weights give the aligned ones' result to rounding."""
+    from paper_2102_02019_amd import labfm
+
+    prm = inputs.taylor_green_params()
+    for seed in range(1, 100):
+        nodes = inputs.jittered_lattice(17, seed=seed, m=4)
+        nodes.h = nodes.h * np.random.default_rng(seed).uniform(0.95, 1.05, nodes.n)
+        x, y, h, s = (T(getattr(nodes, k), dev) for k in ("x", "y", "h", "s"))
+        rp, col = labfm.build_neighbours(x, y, h, nodes.box)
+        if col.numel() % 2 == int(odd):
+            break
+    ops = labfm.build_weights(x, y, h, s, 4, nodes.box, rp, col, rowsum=True)
+    assert ops.nnz % 2 == int(odd)
+    rng = np.random.default_rng(5)
+    rho, u, v = inputs.taylor_green_state(nodes.x, nodes.y)
+    q0 = T(np.concatenate([np.log(rho), u, v]), dev)
+    vec, bar = T(rng.standard_normal(3 * nodes.n), dev), T(rng.standard_normal(3 * nodes.n), dev)
+    dt, eps = 0.05 * float(nodes.s[0]), 1e-6
+    ends = []
+    for sign in (1.0, -1.0):
+        q = q0 + sign * eps * vec
+        labfm.rk_step(q, ops, prm, dt, steps, filter=filt)
+        ends.append(q)
+    jv = float(torch.dot((ends[0] - ends[1]) / (2.0 * eps), bar))
+    grad = labfm.rk_adjoint(q0, bar, ops, prm, dt, steps, ckpt_every=ckpt, filter=filt)
+    scale = float(torch.linalg.norm(grad) * torch.linalg.norm(vec))
+    assert abs(jv - float(torch.dot(vec, grad))) <= 1e-7 * scale
+    tptr, tsrc, tw = ops.transpose
+    off = torch.empty(tw.numel() + 1, dtype=tw.dtype, device=dev)[1:]
+    off.copy_(tw)
+    ops.transpose = (tptr, tsrc, off)
+    again = labfm.rk_adjoint(q0, bar, ops, prm, dt, steps, ckpt_every=ckpt, filter=filt)
+    assert torch.linalg.norm(again - grad) <= 1e-13 * torch.linalg.norm(grad)
+    ops.transpose, ops.use_tiles = (tptr, tsrc, tw), False
+    again = labfm.rk_adjoint(q0, bar, ops, prm, dt, steps, ckpt_every=ckpt, filter=filt)
+    assert torch.linalg.norm(again - grad) <= 1e-12 * torch.linalg.norm(grad)

@@ -528,15 +528,6 @@ struct NbrPrefetch {
 // waves of the workgroup pass through different sequences of barriers.
 __device__ __forceinline__ int uniform(int v) { return __builtin_amdgcn_readfirstlane(v); }
 
-// Workgroup barrier that orders LDS only: the workgroup shares no global
-// data within a node (positions are read-only, each weight is written by one
-// thread), so outstanding global loads and stores stay in flight across it
-// (a full __syncthreads waits for all of them).
-__device__ __forceinline__ void lds_barrier() {
-  __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup", "local");
-  __builtin_amdgcn_s_barrier();
-  __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup", "local");
-}
 __device__ __forceinline__ unsigned long long uniform64(unsigned long long v) {
   const unsigned lo = __builtin_amdgcn_readfirstlane(static_cast<unsigned>(v));
   const unsigned hi = __builtin_amdgcn_readfirstlane(static_cast<unsigned>(v >> 32));

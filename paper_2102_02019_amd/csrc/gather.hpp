@@ -172,75 +172,94 @@ __device__ __forceinline__ T stream_load(const T* p) {
   }
 }
 
-// Edges per lane whose loads are issued together in the gather loops.
+// Edges per lane whose loads are issued together in the untiled and single-edge
+// gather loops of the stage and the filter.
 __host__ __device__ constexpr int unroll_of(int lpn) { return lpn >= 32 ? 3 : (lpn >= 16 ? 3 : 4); }
 
 // --------------------------------------------------------------------------
 // operator application
 // --------------------------------------------------------------------------
 
-template <int LPN, int FL, class P>
+// Bound by the weights, 8 bytes per edge and operator, as long as enough of
+// them are in flight: the number of operators is a template parameter so that
+// the loads of all of them are issued together. (Tested one by one inside the
+// loop, each operator's loads waited for those of the operator before.)
+// 90,601 nodes, K = 60, five operators, float64 (241 MB): 58.7 -> 50 us with the
+// weights in HBM (4.1 -> 4.8 TB/s), 37.7 us where they stay in the last-level
+// cache; 262,144 nodes 160 -> 134 us (5.2 TB/s).
+// U edges per lane and pass: with 4 to 8 lanes 4 (one 32-byte or 64-byte run
+// each), with 16 lanes 2; with 32 lanes 2, or 3 where a row has more than 64
+// edges, so that a row of up to 96 is one pass (K = 90: 66 us with 3, 75 with 2;
+// K = 60: 38 and 37.5).
+
+// The operators an application sums (ascending) and the row of the output each
+// one is written to, -1 for a sum that only the moment correction needs.
+struct ApplyOps {
+  int op[LABFM_NUM_OPS];
+  int row[LABFM_NUM_OPS];
+};
+
+template <int NO, int U, int LPN, int FL, class P>
 __global__ void __launch_bounds__(256)
 apply_kernel(const int* __restrict__ row_ptr, const int* __restrict__ col,
              const typename P::W* __restrict__ w, const float* __restrict__ mom, long long nnz,
-             unsigned mask, const double* __restrict__ phi, double* __restrict__ out, int n) {
+             ApplyOps ops, const double* __restrict__ phi, double* __restrict__ out, int n) {
   const int gid = first_thread<FL>();
   const int node = gid / LPN;
   const int sub = gid % LPN;
   if (node >= n) return;  // whole LPN groups exit together
-  constexpr unsigned kSecond = (1u << LABFM_OP_L) | (1u << LABFM_OP_XX) | (1u << LABFM_OP_XY);
-  constexpr unsigned kFirst = (1u << LABFM_OP_X) | (1u << LABFM_OP_Y);
-  // the moment correction needs the x and y sums
-  const unsigned need = (P::kMomentFix && (mask & kSecond)) ? (mask | kFirst) : mask;
   const int e0 = row_ptr[node], e1 = row_ptr[node + 1];
   const double pi = phi[node];
-  typename P::Acc acc[LABFM_NUM_OPS];
+  typename P::Acc acc[NO];
 #pragma unroll
-  for (int d = 0; d < LABFM_NUM_OPS; ++d) acc[d].zero();
-  constexpr int U = unroll_of(LPN);
-  if (e1 > e0) {
-    for (int base = e0 + sub; base < e1; base += U * LPN) {
-      int ee[U];
-      bool ok[U];
-      typename P::D dj[U];
+  for (int i = 0; i < NO; ++i) acc[i].zero();
+  const typename P::W* wo[NO];
 #pragma unroll
-      for (int u = 0; u < U; ++u) {
-        const int e = base + u * LPN;
-        ok[u] = e < e1;
-        ee[u] = ok[u] ? e : e1 - 1;
-      }
+  for (int i = 0; i < NO; ++i) wo[i] = w + ops.op[i] * wstride<P>(nnz);
+  for (int base = e0 + sub; base < e1; base += U * LPN) {
+    int ee[U], jj[U];
+    bool ok[U];
+    typename P::W wv[NO][U];
+    typename P::D dj[U];
 #pragma unroll
-      for (int u = 0; u < U; ++u) dj[u] = P::diff(phi[stream_load<FL>(col + ee[u])], pi);
+    for (int u = 0; u < U; ++u) {
+      const int e = base + u * LPN;
+      ok[u] = e < e1;
+      ee[u] = ok[u] ? e : e1 - 1;
+      jj[u] = stream_load<FL>(col + ee[u]);
+    }
 #pragma unroll
-      for (int d = 0; d < LABFM_NUM_OPS; ++d) {
-        if (need & (1u << d)) {
-          typename P::W wv[U];
+    for (int i = 0; i < NO; ++i) {
 #pragma unroll
-          for (int u = 0; u < U; ++u)
-            wv[u] = stream_load<FL>(w + d * wstride<P>(nnz) + ee[u]);
+      for (int u = 0; u < U; ++u) wv[i][u] = stream_load<FL>(wo[i] + ee[u]);
+    }
 #pragma unroll
-          for (int u = 0; u < U; ++u) acc[d].add(ok[u] ? wv[u] : typename P::W(0), dj[u]);
-        }
-      }
+    for (int u = 0; u < U; ++u) dj[u] = P::diff(phi[jj[u]], pi);
+#pragma unroll
+    for (int i = 0; i < NO; ++i) {
+      // every load of the pass before the first use, operator by operator
+      // (left to itself the compiler interleaves them and holds fewer in flight)
+      if constexpr (U * NO > 12) __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+      for (int u = 0; u < U; ++u) acc[i].add(ok[u] ? wv[i][u] : typename P::W(0), dj[u]);
     }
   }
-  double v[LABFM_NUM_OPS];
+  double v[NO];
 #pragma unroll
-  for (int d = 0; d < LABFM_NUM_OPS; ++d)
-    v[d] = (need & (1u << d)) ? acc[d].template reduce<LPN>() : 0.0;
+  for (int i = 0; i < NO; ++i) v[i] = acc[i].template reduce<LPN>();
   if (sub != 0) return;
-  if constexpr (P::kMomentFix) {
-    if (mask & kSecond)
-      moment_fix(mom, node, n, v[LABFM_OP_X], v[LABFM_OP_Y], v[LABFM_OP_L], v[LABFM_OP_XX],
-                 v[LABFM_OP_XY]);
-  }
-  int k = 0;
 #pragma unroll
-  for (int d = 0; d < LABFM_NUM_OPS; ++d) {
-    if (mask & (1u << d)) {
-      out[static_cast<long long>(k) * n + node] = v[d];
-      ++k;
+  for (int i = 0; i < NO; ++i) {
+    if (ops.row[i] < 0) continue;
+    if constexpr (P::kMomentFix && NO >= 3) {
+      // with a second derivative the x and y sums come first
+      const int d = ops.op[i];
+      if (d >= LABFM_OP_L && d <= LABFM_OP_XY) {
+        const float* m = mom + 2 * (d - LABFM_OP_L) * static_cast<long long>(n) + node;
+        v[i] -= v[0] * static_cast<double>(m[0]) + v[1] * static_cast<double>(m[n]);
+      }
     }
+    out[ops.row[i] * static_cast<long long>(n) + node] = v[i];
   }
 }
 
@@ -1281,6 +1300,11 @@ LaunchCfg default_cfg(int kernel, labfm_prec prec, int n, long long nnz) {
   // nodes per workgroup, 197 us against 200 us for 16 at 262,144 nodes,
   // K = 90; float32: the quad loads then cover whole 128-byte lines)
   if (kernel == LABFM_KERNEL_STAGE && k > 48.0) lpn = 8;
+  // application: 32 lanes where they take a row in one pass of full runs
+  // (float64, K = 60: 37.5 us against 39.4 with 16 lanes and 43.6 with 8 at
+  // 90,601 nodes; float32, 4 bytes a lane: 29.0 against 26.4 at K = 60, but
+  // 35.1 against 40.3 at K = 90)
+  if (kernel == LABFM_KERNEL_APPLY && k > (prec == LABFM_F64 ? 48.0 : 64.0)) lpn = 32;
   return LaunchCfg{lpn, 0};
 }
 
@@ -1298,11 +1322,37 @@ hipError_t launch_apply(LaunchCfg cfg, const labfm_operators* o, const typename 
                         unsigned mask, const double* phi, double* out, hipStream_t st) {
   const int n = o->n;
   const unsigned grid = blocks_for(static_cast<long long>(n) * cfg.lpn, kThreads);
-  return with_cfg(cfg, [&](auto L, auto F) {
-    hipLaunchKernelGGL((apply_kernel<decltype(L)::value, decltype(F)::value, P>), dim3(grid),
-                       dim3(kThreads), 0, st, o->row_ptr, o->col, w, o->mom32,
-                       static_cast<long long>(o->nnz), mask, phi, out, n);
-  });
+  constexpr unsigned kSecond = (1u << LABFM_OP_L) | (1u << LABFM_OP_XX) | (1u << LABFM_OP_XY);
+  constexpr unsigned kFirst = (1u << LABFM_OP_X) | (1u << LABFM_OP_Y);
+  // the moment correction of a second derivative needs the x and y sums
+  const unsigned need = (P::kMomentFix && (mask & kSecond)) ? (mask | kFirst) : mask;
+  ApplyOps ops{};
+  int count = 0, rows = 0;
+  for (int d = 0; d < LABFM_NUM_OPS; ++d) {
+    if (!(need & (1u << d))) continue;
+    ops.op[count] = d;
+    ops.row[count++] = (mask & (1u << d)) ? rows++ : -1;
+  }
+  const auto run = [&](auto C) {
+    return with_cfg(cfg, [&](auto L, auto F) {
+      constexpr int NO = decltype(C)::value, lpn = decltype(L)::value, fl = decltype(F)::value;
+      const auto kernel = (lpn == 32 && o->nnz > 64LL * n)
+                              ? apply_kernel<NO, 3, lpn, fl, P>
+                              : apply_kernel<NO, (lpn <= 8 ? 4 : 2), lpn, fl, P>;
+      hipLaunchKernelGGL(
+          kernel, dim3(grid), dim3(kThreads), 0, st, o->row_ptr, o->col, w, o->mom32,
+          static_cast<long long>(o->nnz), ops, phi, out, n);
+    });
+  };
+  using std::integral_constant;
+  switch (count) {
+    case 1: return run(integral_constant<int, 1>{});
+    case 2: return run(integral_constant<int, 2>{});
+    case 3: return run(integral_constant<int, 3>{});
+    case 4: return run(integral_constant<int, 4>{});
+    case 5: return run(integral_constant<int, 5>{});
+    default: return run(integral_constant<int, 6>{});
+  }
 }
 
 Tiles tiles_of(const labfm_operators* o, bool reverse) {

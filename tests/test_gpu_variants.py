@@ -238,3 +238,55 @@ def test_adjoint_against_differences(dev, odd, steps, ckpt, filt):
     ops.transpose, ops.use_tiles = (tptr, tsrc, tw), False
     again = labfm.rk_adjoint(q0, bar, ops, prm, dt, steps, ckpt_every=ckpt, filter=filt)
     assert torch.linalg.norm(again - grad) <= 1e-12 * torch.linalg.norm(grad)
+
+
+# 16 lanes take 32 edges a pass, 32 lanes 64, or 96 where the mean exceeds 64,
+# 8 lanes 32, 4 lanes 16: rows around each; none, one and several operators
+@pytest.mark.parametrize("rows", [(0, 1, 3, 15, 16, 17, 4), (0, 31, 32, 33, 63, 64, 65, 2),
+                                  (95, 96, 97, 191, 0, 193, 1)])
+@pytest.mark.parametrize("prec_name", ["F64", "F32W", "F32_COMP"])
+def test_operator_subsets_and_row_lengths(dev, rows, prec_name):
+    """Every number of operators and every lane count against numpy, within the
+    rounding of a sum of K products: 2 K eps of the summed magnitudes, (K eps32)^2
+    times four for the compensated float32 sums."""
+    from paper_2102_02019_amd import labfm
+
+    prec = getattr(labfm, prec_name)
+    rng = np.random.default_rng(17)
+    cnt = np.array(rows * 3 + rows[:2])
+    n, rp = cnt.size, np.concatenate([[0], np.cumsum(cnt)])
+    nnz, kmax = int(rp[-1]), int(cnt.max())
+    col = rng.integers(0, n, nnz)
+    w, phi = rng.standard_normal((6, nnz)), rng.standard_normal(n)
+    mom = (1e-3 * rng.standard_normal((6, n))).astype(np.float32)
+    stride = int(labfm.lib().labfm_w32_stride(nnz))
+    w32 = torch.zeros((6, stride), dtype=torch.float32, device=dev)
+    w32[:, :nnz] = T(w.astype(np.float32), dev)
+    ops = labfm.Operators(T(rp.astype(np.int32), dev), T(col.astype(np.int32), dev), T(w, dev),
+                          w32[:, :nnz], T(np.zeros(n), dev), mom32=T(mom, dev))
+    f32 = prec_name != "F64"
+    wd = (w.astype(np.float32) if f32 else w).astype(np.float64)
+    d = phi[col] - np.repeat(phi, cnt)
+    row = np.repeat(np.arange(n), cnt)
+    ref, mag = np.zeros((6, n)), np.zeros((6, n))
+    for k in range(6):
+        np.add.at(ref[k], row, wd[k] * d)
+        np.add.at(mag[k], row, np.abs(wd[k] * d))
+    if f32:
+        for k in (2, 3, 4):
+            mx, my = mom[2 * (k - 2)].astype(np.float64), mom[2 * (k - 2) + 1].astype(np.float64)
+            ref[k] -= ref[0] * mx + ref[1] * my
+            mag[k] += mag[0] * np.abs(mx) + mag[1] * np.abs(my)
+    eps = 2 * (kmax + 4) * 2.0 ** -53
+    if prec_name == "F32_COMP":
+        eps += 4 * ((kmax + 4) * 2.0 ** -24) ** 2
+    try:
+        for lpn in (0, 4, 8, 16, 32):
+            labfm.set_launch_config(labfm.KERNEL_APPLY, prec, lpn, 0)
+            for mask in (0x01, 0x20, 0x10, 0x06, 0x1C, 0x2D, 0x1F, 0x3F):
+                got = labfm.apply_operators(ops, T(phi, dev), mask, prec).cpu().numpy()
+                sel = [k for k in range(6) if mask >> k & 1]
+                bad = np.abs(got.reshape(len(sel), n) - ref[sel]) > eps * mag[sel]
+                assert not bad.any(), (lpn, hex(mask))
+    finally:
+        labfm.set_launch_config(labfm.KERNEL_APPLY, prec, 0, 0)

@@ -8,8 +8,12 @@
 // per-edge index stream (2 instead of 4 bytes).
 //
 // One workgroup builds one tile: the row entries are inserted into an LDS
-// hash set, the distinct indices are sorted (bitonic sort in LDS), and every
-// entry's position in the sorted halo is found by binary search.
+// hash set, each distinct index is ranked by counting the smaller ones (its
+// position in the sorted halo), and every entry reads its position from the
+// set. The list is short (K = 90: 260 of at most 1024 slots), so counting, four
+// indices per broadcast read and no barriers, replaces a bitonic sort of all
+// 1024 slots (55 barriers) and the binary search of every entry: 234 -> 94 us at
+// 262,144 nodes, 61 -> 35 us at 40,000 with mixed orders.
 #include <climits>
 
 #include "common.hpp"
@@ -34,35 +38,32 @@ build_tiles_kernel(const int* __restrict__ row_ptr, const int* __restrict__ col,
                    unsigned short* __restrict__ lcol, int* __restrict__ max_halo,
                    int* __restrict__ overflow) {
   __shared__ int table[kHashCap];
-  __shared__ int list[kHashCap];
+  __shared__ unsigned short rank_at[kHashCap];  // position of the index in each slot
+  __shared__ unsigned short slot_of[kHaloMax];
+  __shared__ alignas(16) int list[kHaloMax];
   __shared__ int s_count;
-  __shared__ int s_full;
   const int t = blockIdx.x;
   const int tid = threadIdx.x;
   const int t0 = t * kTileNodes;
   const int t1 = min(n, t0 + kTileNodes);
   const int e0 = row_ptr[t0], e1 = row_ptr[t1];
-  for (int k = tid; k < kHashCap; k += kThreads) {
-    table[k] = kEmpty;
-    list[k] = INT_MAX;
-  }
-  if (tid == 0) {
-    s_count = 0;
-    s_full = 0;
-  }
+  for (int k = tid; k < kHashCap; k += kThreads) table[k] = kEmpty;
+  for (int k = tid; k < kHaloMax; k += kThreads) list[k] = INT_MAX;
+  if (tid == 0) s_count = 0;
   __syncthreads();
-  // insert every neighbour index (linear probing; duplicates stop at their slot)
+  // insert every neighbour index (linear probing; duplicates stop at their
+  // slot, most of them at the plain read)
   for (int e = e0 + tid; e < e1; e += kThreads) {
     const int j = col[e];
     unsigned sl = hash_slot(j);
     for (int probe = 0; probe < kHashCap; ++probe) {
-      const int prev = atomicCAS(&table[sl], kEmpty, j);
+      int prev = table[sl];
+      if (prev == kEmpty) prev = atomicCAS(&table[sl], kEmpty, j);
       if (prev == kEmpty) {
         const int pos = atomicAdd(&s_count, 1);
         if (pos < kHaloMax) {
           list[pos] = j;
-        } else {
-          s_full = 1;
+          slot_of[pos] = static_cast<unsigned short>(sl);
         }
         break;
       }
@@ -72,49 +73,36 @@ build_tiles_kernel(const int* __restrict__ row_ptr, const int* __restrict__ col,
   }
   __syncthreads();
   const int count = s_count;
-  if (s_full || count > kHaloMax) {
+  if (count > kHaloMax) {
     if (tid == 0) {
       atomicMax(overflow, 1);
       halo_count[t] = 0;
     }
     return;
   }
-  // bitonic sort of list[0 .. kHaloMax) ascending (unused entries are INT_MAX)
-  for (int size = 2; size <= kHaloMax; size <<= 1) {
-    for (int stride = size >> 1; stride > 0; stride >>= 1) {
-      for (int k = tid; k < kHaloMax; k += kThreads) {
-        const int p = k ^ stride;
-        if (p > k) {
-          const bool up = (k & size) == 0;
-          const int a = list[k], b = list[p];
-          if ((a > b) == up) {
-            list[k] = b;
-            list[p] = a;
-          }
-        }
-      }
-      __syncthreads();
+  for (int k = tid; k < count; k += kThreads) {
+    const int j = list[k];
+    int rank = 0;
+    for (int i = 0; i < count; i += 4) {  // slots past the count hold INT_MAX
+      const int4 o = *reinterpret_cast<const int4*>(list + i);
+      rank += (o.x < j) + (o.y < j) + (o.z < j) + (o.w < j);
     }
+    halo_idx[static_cast<long long>(t) * kHaloMax + rank] = j;
+    rank_at[slot_of[k]] = static_cast<unsigned short>(rank);
   }
-  for (int k = tid; k < count; k += kThreads)
-    halo_idx[static_cast<long long>(t) * kHaloMax + k] = list[k];
   if (tid == 0) {
     halo_count[t] = count;
-    atomicMax(max_halo, count);
+    // (the plain read may be old, which only costs an atomic; one per tile on
+    // the same address takes 10 ns each)
+    if (count > *max_halo) atomicMax(max_halo, count);
   }
+  __syncthreads();
   // position of every entry in the sorted halo
   for (int e = e0 + tid; e < e1; e += kThreads) {
     const int j = col[e];
-    int lo = 0, hi = count - 1;
-    while (lo < hi) {
-      const int mid = (lo + hi) >> 1;
-      if (list[mid] < j) {
-        lo = mid + 1;
-      } else {
-        hi = mid;
-      }
-    }
-    lcol[e] = static_cast<unsigned short>(lo);
+    unsigned sl = hash_slot(j);
+    while (table[sl] != j) sl = (sl + 1) & (kHashCap - 1);  // it was inserted above
+    lcol[e] = rank_at[sl];
   }
 }
 

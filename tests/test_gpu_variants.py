@@ -290,3 +290,34 @@ def test_operator_subsets_and_row_lengths(dev, rows, prec_name):
                 assert not bad.any(), (lpn, hex(mask))
     finally:
         labfm.set_launch_config(labfm.KERNEL_APPLY, prec, 0, 0)
+
+
+# distinct neighbours of the first tile: one, around a group of four, around
+# the workgroup's 256 threads, the capacity, and one and many past it; the
+# second tile holds one node
+@pytest.mark.parametrize("distinct", [1, 4, 5, 255, 257, 1023, 1024, 1025, 3000])
+@pytest.mark.parametrize("step", [1, 2048])
+def test_tile_halos(dev, distinct, step):
+    """The halo is the sorted set of a tile's neighbours and every entry finds
+    its own index through it; consecutive and widely spaced indices (runs in
+    the hash table), each neighbour listed up to four times."""
+    from paper_2102_02019_amd import labfm
+
+    n = labfm.TILE_NODES + 1
+    rng = np.random.default_rng(distinct + step)
+    base = step * np.arange(distinct, dtype=np.int64) + 7
+    first = rng.permutation(np.concatenate([base, base[::2], base[::2], base[:3]]))
+    cuts = np.sort(rng.integers(0, first.size + 1, labfm.TILE_NODES - 1))
+    rp = np.concatenate([[0], cuts, [first.size, first.size + 2]])
+    col = np.concatenate([first, [5, 3]])
+    ops = labfm.Operators(T(rp.astype(np.int32), dev), T(col.astype(np.int32), dev), None, None,
+                          torch.zeros(n, dtype=torch.float64, device=dev))
+    ok = labfm.build_tiles(ops)
+    assert ok == (distinct <= labfm.TILE_HALO_MAX)
+    if not ok:
+        return
+    hc, hi, lc, hmax = (v.cpu().numpy() if torch.is_tensor(v) else v for v in ops.tiles)
+    halo = hi.reshape(2, -1)
+    assert hc.tolist() == [distinct, 2] and hmax == max(distinct, 2)
+    assert np.array_equal(halo[0, :distinct], base) and halo[1, :2].tolist() == [3, 5]
+    assert np.array_equal(halo[0, lc[:first.size]], first) and lc[first.size:].tolist() == [1, 0]

@@ -224,14 +224,19 @@ def _check(code: int) -> None:
         raise LabfmError(code, lib().labfm_last_error().decode())
 
 
-def _ptr(t: Optional[torch.Tensor]):
+def _addr(t: Optional[torch.Tensor]) -> Optional[int]:
+    """Device address of a tensor, as a pointer argument or field takes it."""
     if t is None:
         return None
     if not t.is_cuda:
         raise ValueError("labfm expects HIP device tensors")
     if not t.is_contiguous():
         raise ValueError("labfm expects contiguous tensors")
-    return ctypes.c_void_p(t.data_ptr())
+    return t.data_ptr()
+
+
+def _ptr(t: Optional[torch.Tensor]):
+    return None if t is None else ctypes.c_void_p(_addr(t))
 
 
 def _w32_ptr(t: Optional[torch.Tensor]):
@@ -247,7 +252,8 @@ def _w32_ptr(t: Optional[torch.Tensor]):
 
 
 def _stream():
-    return ctypes.c_void_p(torch.cuda.current_stream().cuda_stream)
+    # the raw handle: a Stream object costs as much as the rest of a small call
+    return ctypes.c_void_p(torch._C._cuda_getCurrentRawStream(torch.cuda.current_device()))
 
 
 def _workspace(nbytes: int, device) -> torch.Tensor:
@@ -336,15 +342,12 @@ class Operators:
         tp = None
         if self.tiles is not None and self.use_tiles:
             hc, hi, lc, hmax = self.tiles
-            self._ctiles = _Tiles(hc.numel(), hmax, _ptr(hc).value, _ptr(hi).value,
-                                  _ptr(lc).value)
+            self._ctiles = _Tiles(hc.numel(), hmax, _addr(hc), _addr(hi), _addr(lc))
             tp = ctypes.pointer(self._ctiles)
-        return _Operators(self.n, self.nnz, _ptr(self.row_ptr).value, _ptr(self.col).value,
-                          None if self.w is None else _ptr(self.w).value,
+        return _Operators(self.n, self.nnz, _addr(self.row_ptr), _addr(self.col),
+                          _addr(self.w),
                           None if self.w32 is None else _w32_ptr(self.w32).value,
-                          None if self.mom32 is None else _ptr(self.mom32).value,
-                          _ptr(self.kappa).value, tp,
-                          None if self.wall_normal is None else _ptr(self.wall_normal).value)
+                          _addr(self.mom32), _addr(self.kappa), tp, _addr(self.wall_normal))
 
 
 def w32_stride(nnz: int) -> int:
@@ -498,7 +501,7 @@ def apply_operators(ops: Operators, phi: torch.Tensor, op_mask: int = 0x3F,
     k = bin(op_mask).count("1")
     out = torch.empty((k, ops.n), dtype=torch.float64, device=phi.device)
     c = ops._c()
-    _check(lib().labfm_apply_operators(ctypes.byref(c), op_mask, _ptr(phi), _ptr(out), prec,
+    _check(lib().labfm_apply_operators(ctypes.byref(c), op_mask, _addr(phi), _addr(out), prec,
                                        _stream()))
     return out
 

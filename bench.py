@@ -707,7 +707,7 @@ def lagrangian_bench(args, inputs, labfm, torch, np, dev, rk_steps=10):
         "stage_and_filter_ms_per_job": stage_ms,
         "max_nnz": stats[-1]["max_nnz"], "nnz_capacity": cap,
         "final_state_finite": finite,
-        "roofline": {"bound": "mfma", "kernel": build_kernel_name(labfm, wl.m),
+        "roofline": {"bound": "mfma", "kernel": build_kernel_name(labfm, wl.m, N),
                      "achieved": br["achieved_TFLOPs"], "peak": FP64_PEAK_TFLOPS,
                      "unit": "TFLOP/s", "frac": br["frac"], "traffic": None,
                      "gflop_per_build": br["gflop"], "mean_build_ms": br["weights_ms"]},
@@ -996,12 +996,14 @@ def stream_copy_rate(torch, dev, reps=5):
             "read_ms": t_sum, "bytes": nb, "frac_of_hbm_peak": best / HBM_PEAK_GBS}
 
 
-def build_kernel_name(labfm, m):
-    """The weight-build kernel the library launches for order m under the
-    installed distribution: one wavefront per node with the rows in
-    registers for orders up to 10 (the default), else the workgroup-per-node
-    kernel."""
+def build_kernel_name(labfm, m, count):
+    """The weight-build kernel the library launches for count nodes of order m
+    under the installed distribution: the rows in registers for orders up to
+    10 (the default; several nodes per wavefront at orders 1 to 6 from 8,192
+    nodes on), else the workgroup-per-node kernel."""
     mode = labfm.get_build_config()[0]
+    if mode == labfm.BUILD_ROWS and m <= 6 and count >= 8192:
+        return "build_group_kernel<%d, 6>" % m
     if mode == labfm.BUILD_ROWS and m <= 10:
         return "build_rows_kernel<%d>" % m
     return "build_block_kernel<%d>" % m
@@ -1041,7 +1043,8 @@ def build_rate(labfm, torch, np, nodes, x, y, h, s, m):
             "distribution": {1: "wavefront-per-node", 2: "workgroup-per-node",
                              3: "persistent", 4: "per-order-class",
                              5: "rows-in-registers"}.get(mode[0], str(mode[0])),
-            "kernel": build_kernel_name(labfm, int(np.max(nodes.m)))}
+            "kernel": build_kernel_name(labfm, int(np.max(nodes.m)),
+                                        int(np.count_nonzero(nodes.m == np.max(nodes.m))))}
 
 
 def _oracle_sample(args):

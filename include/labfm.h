@@ -295,9 +295,8 @@ int labfm_fill_neighbours(const double* x, const double* y, const double* h, int
  * kappa = 0 except for LABFM_NODE_FEW_NEIGHBOURS, whose weights are those of
  * the (rank-deficient) solve when it completes. Nodes of different orders and
  * stencil sizes are built in one call; labfm_set_build_config selects how
- * they are spread over the GPU (default LABFM_BUILD_ROWS: one wavefront per
- * node holding the system's rows in registers, from a work list grouped by
- * order; labfm_tune_build picks). Synchronises once (the launches are sized on the
+ * they are spread over the GPU (default LABFM_BUILD_ROWS: the systems' rows in
+ * the registers of a wavefront, from a work list grouped by order; labfm_tune_build picks). Synchronises once (the launches are sized on the
  * host from the order histogram); the build kernels are enqueued after that.
  */
 size_t labfm_build_workspace_bytes(int32_t n);
@@ -337,7 +336,7 @@ int labfm_build_weights_noalloc(const double* x, const double* y, const double* 
  * given systems M~ Psi = C~ (section "The Local Anisotropic Basis Function
  * Method", the linear system of each node and its solution by LU with
  * partial pivoting): the rows-in-registers kernel of LABFM_BUILD_ROWS runs
- * them in place of the systems it assembles, one wavefront per system, so
+ * them in place of the systems it assembles, distributed as in the build, so
  * its pivot rule and solution can be checked against a host solver.
  *
  *   m          order 1..10; n = (m^2+3m)/2.
@@ -393,8 +392,8 @@ int labfm_solve_systems(int32_t m, const double* systems, int32_t count, double*
  *   iters              int32[n] output k with h_out = h0 shrink^k (by repeated
  *                      multiplication), or NULL.
  *   workspace          labfm_optimise_workspace_bytes(n, nnz) bytes: the node
- *                      list, one pass's x, y and L weights (3 nnz doubles)
- *                      and the per-node state.
+ *                      lists of two passes, one pass's x, y and L weights
+ *                      (3 nnz doubles) and the per-node state.
  * Nodes with orders outside 1..10 keep h0. Synchronises once to size the
  * launches, then once per pass (to see whether any node is still shrinking).
  */
@@ -485,9 +484,10 @@ enum {
   LABFM_BUILD_PERSISTENT = 3,  /* one launch of persistent 256-thread workgroups taking
                                   nodes (highest order first) from a work counter */
   LABFM_BUILD_BUCKETED = 4,    /* one 256-thread-per-node launch per order class */
-  LABFM_BUILD_ROWS = 5         /* one 64-lane wavefront per node holding the system's
-                                  rows in registers (orders 1..10, one launch per
-                                  order present; at order 10 the pivot row of the
+  LABFM_BUILD_ROWS = 5         /* a system's rows in registers, one node per 64-lane
+                                  wavefront, or two or four at orders 1..6 where
+                                  8192 nodes or more share an order (orders 1..10,
+                                  one launch per order present; at order 10 the pivot row of the
                                   first column is kept in LDS and the other 64
                                   rows fill the lanes);
                                   out-of-range orders take the workgroup-per-node

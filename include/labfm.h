@@ -393,7 +393,8 @@ int labfm_solve_systems(int32_t m, const double* systems, int32_t count, double*
  *                      multiplication), or NULL.
  *   workspace          labfm_optimise_workspace_bytes(n, nnz) bytes: the node
  *                      lists of two passes, one pass's x, y and L weights
- *                      (3 nnz doubles) and the per-node state.
+ *                      (3 nnz doubles), the neighbours still in reach (nnz
+ *                      ints) and the per-node state.
  * Nodes with orders outside 1..10 keep h0. Synchronises once to size the
  * launches, then once per pass (to see whether any node is still shrinking).
  */

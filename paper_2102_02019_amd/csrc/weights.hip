@@ -456,6 +456,7 @@ struct BuildArgs {
   int n;
   labfm_box box;
   const int* row_ptr;
+  const int* row_end;  // one past each row's last entry (row_ptr + 1 for a whole CSR)
   const int* col;
   long long nnz;
   double* w;
@@ -893,7 +894,7 @@ __device__ void build_node_block(int i_in, const BuildArgs& g, BlockSmem<MMAX>& 
   const int i = uniform(i_in);
   const int m = uniform(g.order[i]);
   const int e0 = uniform(g.row_ptr[i]);
-  const int K = uniform(g.row_ptr[i + 1]) - e0;
+  const int K = uniform(g.row_end[i]) - e0;
   // one exit: every path below ends at the final barrier, and every branch
   // around a barrier depends on wave-uniform values only
   const bool valid = (m >= 1 && m <= MMAX);
@@ -1619,7 +1620,7 @@ __device__ __forceinline__ void rows_node(BuildArgs g, const int* __restrict__ l
   const int lane = threadIdx.x;
   const int i = kSolve ? k_ : uniform(list ? list[k_] : k_);
   const int e0 = kSolve ? 0 : uniform(g.row_ptr[i]);
-  const int K = kSolve ? N : uniform(g.row_ptr[i + 1]) - e0;
+  const int K = kSolve ? N : uniform(g.row_end[i]) - e0;
   const double xi = kSolve ? 0.0 : g.x[i], yi = kSolve ? 0.0 : g.y[i];
   const double h = kSolve ? 1.0 : g.h[i];
   const double hinv = 1.0 / h;
@@ -2041,7 +2042,7 @@ __device__ __forceinline__ void group_nodes(BuildArgs g, const int* __restrict__
       const int i = node_of(q);
       if (i >= 0) {
         const int e0 = uniform(g.row_ptr[i]);
-        const int K = uniform(g.row_ptr[i + 1]) - e0;
+        const int K = uniform(g.row_end[i]) - e0;
         assemble_tiles<M, NB, NB>(g, e0, K, g.x[i], g.y[i], 1.0 / g.h[i], ea, eb, 0, NB, sm.buf,
                                   acc[q]);
       }
@@ -2232,7 +2233,7 @@ __device__ __forceinline__ void group_nodes(BuildArgs g, const int* __restrict__
       const int i = node_of(q);
       if (i < 0) continue;
       const int e0 = uniform(g.row_ptr[i]);
-      const int K = uniform(g.row_ptr[i + 1]) - e0;
+      const int K = uniform(g.row_end[i]) - e0;
       if ((bad >> (q * GW)) & 1) {
         node_singular<NOPS>(i, e0, K);
       } else {
@@ -2338,7 +2339,10 @@ struct OptArgs {
   const int8_t* order;
   labfm_box box;
   const int* row_ptr;  // CSR of the h0 stencils
+  const int* row_end;  // this pass's rows: the neighbours still in reach
   const int* col;
+  int* reach;          // the next pass's neighbours and row ends (from row_ptr on)
+  int* reach_end;
   long long nnz;
   const double* w;        // this pass's weights, rows x, y, L ([3][nnz])
   const int8_t* status;   // this pass's build status
@@ -2425,6 +2429,11 @@ __device__ __forceinline__ double halves_sum(double a, double b, int lane) {
 // (operator, wavenumber), a pass over 16,384 nodes of K = 97 took 155 us, all
 // of it issuing instructions; now 76 us.
 //
+// The test also lists the neighbours still in reach for the next pass: at
+// h/s = 1.6 two thirds of the h0 stencil carry zero weights, which a pass then
+// neither assembles nor tests (16,384 nodes of order 6: 16.3 -> 13.7 ms for
+// all passes; each sum keeps its order, so the counts are the same).
+//
 // list: the nodes of order M still shrinking; goes_on[k] says whether list[k]
 // shrinks further.
 template <int M>
@@ -2439,7 +2448,7 @@ stencil_accept_kernel(OptArgs a, const int* __restrict__ list, int count,
   const int i = uniform(list[kn]);
   const int lane = threadIdx.x;
   const int e0 = uniform(a.row_ptr[i]);
-  const int K = uniform(a.row_ptr[i + 1]) - e0;
+  const int K = uniform(a.row_end[i]) - e0;
   const int kcur = uniform(a.k[i]);
   const double h = a.h[i], s = a.s[i], xi = a.x[i], yi = a.y[i];
   const int px = a.box.periodic_x, py = a.box.periodic_y;
@@ -2454,12 +2463,14 @@ stencil_accept_kernel(OptArgs a, const int* __restrict__ list, int count,
 #pragma unroll
   for (int q = 0; q < 3 * kNk; ++q) amp[q] = 0.0;
   // the lane's neighbour, one round ahead
+  int jn = 0;
+  int kept = 0;
   double xn = 0.0, yn = 0.0, wn[3] = {0.0, 0.0, 0.0};
   auto fetch = [&](int k) {
     if (k < K) {
-      const int j = a.col[e0 + k];
-      xn = a.x[j];
-      yn = a.y[j];
+      jn = a.col[e0 + k];
+      xn = a.x[jn];
+      yn = a.y[jn];
 #pragma unroll
       for (int d = 0; d < 3; ++d) wn[d] = a.w[d * a.nnz + e0 + k];
     }
@@ -2467,6 +2478,7 @@ stencil_accept_kernel(OptArgs a, const int* __restrict__ list, int count,
   fetch(lane);
   for (int k0 = 0; k0 < K; k0 += 64) {
     const bool have = k0 + lane < K;
+    const int j = jn;
     const double xj = xn, yj = yn;
     const double w0 = have ? wn[0] : 0.0, w1 = have ? wn[1] : 0.0, w2 = have ? wn[2] : 0.0;
     fetch(k0 + 64 + lane);  // in flight while this round is tested
@@ -2477,6 +2489,14 @@ stencil_accept_kernel(OptArgs a, const int* __restrict__ list, int count,
     }
     {
       const double zx = dx * hinv, zy = dy * hinv;
+      // Out of the kernel's reach (2 h, and by a margin past rounding) at this
+      // scale is out of reach at every smaller one: its weights are zeros, and
+      // the next pass goes without it. The list may be this pass's own: what
+      // this round writes lies before what the prefetch above has read.
+      const bool keep = have && !(zx * zx + zy * zy >= 4.0 * (1.0 + 1e-8));
+      const unsigned long long mask = __builtin_amdgcn_ballot_w64(keep);
+      if (keep) a.reach[e0 + kept + __builtin_popcountll(mask & ((1ull << lane) - 1))] = j;
+      kept += __builtin_popcountll(mask);
       double vx = 1.0, vy = 1.0;
       double* row = sm.tab[lane];
       row[0] = 1.0;
@@ -2568,6 +2588,7 @@ stencil_accept_kernel(OptArgs a, const int* __restrict__ list, int count,
   if (lane == 0) {
     const bool on = ok && kcur <= a.max_iter;
     goes_on[kn] = on ? 1 : 0;
+    a.reach_end[i] = e0 + kept;
     if (on) {
       a.h_out[i] = h;
       a.iters[i] = kcur;
@@ -2807,7 +2828,7 @@ int build_weights_with(const double* x, const double* y, const double* h, const 
       mmax = 15 - b;
       break;
     }
-  const BuildArgs g{x, y, h, s, order_m, n, box, row_ptr, col, nnz, w, w32, mom32, kappa,
+  const BuildArgs g{x, y, h, s, order_m, n, box, row_ptr, row_ptr + 1, col, nnz, w, w32, mom32, kappa,
                     rowsum, status, rows};
   hipError_t e = hipSuccess;
   switch (cfg.mode) {
@@ -3092,7 +3113,7 @@ extern "C" int labfm_tune_build(const double* x, const double* y, const double* 
 // Workspace of labfm_optimise_stencils: the lists of this and the next pass's
 // nodes, the x, y and L weights of a pass, and the per-node state.
 struct OptLayout {
-  size_t list, next, w, h, kappa, k, iters, goes_on, status, total;
+  size_t list, next, w, reach, reach_end, h, kappa, k, iters, goes_on, status, total;
   OptLayout(int32_t n, int64_t nnz) {
     size_t o = 0;
     auto take = [&](size_t bytes) {
@@ -3103,6 +3124,8 @@ struct OptLayout {
     list = take(build_work_bytes(n));
     next = take(build_work_bytes(n));
     w = take(sizeof(double) * 3 * static_cast<size_t>(nnz));
+    reach = take(sizeof(int) * static_cast<size_t>(nnz));
+    reach_end = take(sizeof(int) * static_cast<size_t>(n));
     h = take(sizeof(double) * static_cast<size_t>(n));
     kappa = take(sizeof(double) * static_cast<size_t>(n));
     k = take(sizeof(int) * static_cast<size_t>(n));
@@ -3148,7 +3171,10 @@ extern "C" int labfm_optimise_stencils(const double* x, const double* y, const d
   a.order = order_m;
   a.box = box;
   a.row_ptr = row_ptr;
+  a.row_end = row_ptr + 1;
   a.col = col;
+  a.reach = reinterpret_cast<int*>(base + L.reach);
+  a.reach_end = reinterpret_cast<int*>(base + L.reach_end);
   a.nnz = nnz;
   a.w = reinterpret_cast<double*>(base + L.w);
   a.status = reinterpret_cast<int8_t*>(base + L.status);
@@ -3164,12 +3190,12 @@ extern "C" int labfm_optimise_stencils(const double* x, const double* y, const d
                      a.h, a.k, a.h_out, a.iters);
   LABFM_HIP(hipGetLastError());
   // x, y and L weights of the nodes still shrinking, at their current scales
-  BuildArgs g{x, y, a.h, s, order_m, n, box, row_ptr, col, nnz,
+  BuildArgs g{x, y, a.h, s, order_m, n, box, row_ptr, row_ptr + 1, col, nnz,
               reinterpret_cast<double*>(base + L.w), nullptr, nullptr,
               reinterpret_cast<double*>(base + L.kappa), nullptr,
               reinterpret_cast<int8_t*>(base + L.status),
               rows_of_mask((1u << LABFM_OP_X) | (1u << LABFM_OP_Y) | (1u << LABFM_OP_L))};
-  // Two lists in turn, each with a part per order (order m's at starts[15 - m])
+  // Two node lists in turn, each with a part per order (order m's at starts[15 - m])
   // and the parts' lengths in its first ints: a pass reads one and appends the
   // nodes that go on to the other.
   int* lists[2] = {work, reinterpret_cast<int*>(base + L.next)};
@@ -3202,6 +3228,9 @@ extern "C" int labfm_optimise_stencils(const double* x, const double* y, const d
     }
     LABFM_HIP(hipMemcpyAsync(left, counts, sizeof(left), hipMemcpyDeviceToHost, st));
     LABFM_HIP(hipStreamSynchronize(st));
+    // from the second pass on, the neighbours that were in reach in the one before
+    g.row_end = a.row_end = a.reach_end;
+    g.col = a.col = a.reach;
   }
   set_error("optimise_stencils: %s", "nodes still shrinking after max_iter + 2 passes");
   return LABFM_ERR_HIP;

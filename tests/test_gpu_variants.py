@@ -321,3 +321,34 @@ def test_tile_halos(dev, distinct, step):
     assert hc.tolist() == [distinct, 2] and hmax == max(distinct, 2)
     assert np.array_equal(halo[0, :distinct], base) and halo[1, :2].tolist() == [3, 5]
     assert np.array_equal(halo[0, lc[:first.size]], first) and lc[first.size:].tolist() == [1, 0]
+
+
+# the neighbours in reach shrink from pass to pass (the lists start at some 130
+# and 190 entries: several rounds of 64, the last ones partly filled)
+@pytest.mark.parametrize("m,side", [(4, 23), (6, 33)])
+@pytest.mark.parametrize("wide", [1.2, 1.5])
+def test_optimisation_drops_neighbours_out_of_reach(dev, m, side, wide):
+    """Entries beyond 2 h carry zero weights, so a CSR that lists more of them
+    gives every node the same scale and count."""
+    import ctypes
+
+    from paper_2102_02019_amd import labfm
+
+    nodes = inputs.jittered_lattice(side, seed=side, m=m)
+    x, y, s = T(nodes.x, dev), T(nodes.y, dev), T(nodes.s, dev)
+    mt = torch.full((nodes.n,), m, dtype=torch.int8, device=dev)
+    h0 = (2.2 if m == 4 else 2.8) * s
+    h, it = labfm.optimise_stencils(x, y, s, m, nodes.box, h0=h0)
+    rp, col = labfm.build_neighbours(x, y, wide * h0, nodes.box)
+    h1, it1 = torch.empty_like(h), torch.empty_like(it)
+    ws = torch.empty(labfm.lib().labfm_optimise_workspace_bytes(nodes.n, col.numel()),
+                     dtype=torch.uint8, device=dev)
+    prm = labfm._StencilOptParams(0.99, 1.01, 1e4, 200)
+    code = labfm.lib().labfm_optimise_stencils(
+        x.data_ptr(), y.data_ptr(), h0.data_ptr(), s.data_ptr(), mt.data_ptr(), nodes.n,
+        labfm._box(nodes.box), rp.data_ptr(), col.data_ptr(), col.numel(), ctypes.byref(prm),
+        h1.data_ptr(), it1.data_ptr(), ws.data_ptr(), ws.numel(),
+        torch.cuda.current_stream().cuda_stream)
+    assert code == labfm.OK
+    assert int(it.max()) > 10
+    assert torch.equal(it, it1) and torch.equal(h, h1)

@@ -224,15 +224,18 @@ def _check(code: int) -> None:
         raise LabfmError(code, lib().labfm_last_error().decode())
 
 
-def _addr(t: Optional[torch.Tensor]) -> Optional[int]:
-    """Device address of a tensor, as a pointer argument or field takes it."""
-    if t is None:
-        return None
+def _addr(t: torch.Tensor) -> int:
+    """Device address of a tensor that a call needs, as a pointer argument or
+    field takes it (None is refused: the library does not check every field)."""
     if not t.is_cuda:
         raise ValueError("labfm expects HIP device tensors")
     if not t.is_contiguous():
         raise ValueError("labfm expects contiguous tensors")
     return t.data_ptr()
+
+
+def _opt_addr(t: Optional[torch.Tensor]) -> Optional[int]:
+    return None if t is None else _addr(t)
 
 
 def _ptr(t: Optional[torch.Tensor]):
@@ -345,9 +348,10 @@ class Operators:
             self._ctiles = _Tiles(hc.numel(), hmax, _addr(hc), _addr(hi), _addr(lc))
             tp = ctypes.pointer(self._ctiles)
         return _Operators(self.n, self.nnz, _addr(self.row_ptr), _addr(self.col),
-                          _addr(self.w),
+                          _opt_addr(self.w),
                           None if self.w32 is None else _w32_ptr(self.w32).value,
-                          _addr(self.mom32), _addr(self.kappa), tp, _addr(self.wall_normal))
+                          _opt_addr(self.mom32), _addr(self.kappa), tp,
+                          _opt_addr(self.wall_normal))
 
 
 def w32_stride(nnz: int) -> int:

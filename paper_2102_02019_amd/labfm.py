@@ -256,7 +256,10 @@ def _w32_ptr(t: Optional[torch.Tensor]):
 
 def _stream():
     # the raw handle: a Stream object costs as much as the rest of a small call
-    return ctypes.c_void_p(torch._C._cuda_getCurrentRawStream(torch.cuda.current_device()))
+    raw = getattr(torch._C, "_cuda_getCurrentRawStream", None)  # private to torch
+    if raw is None:
+        return ctypes.c_void_p(torch.cuda.current_stream().cuda_stream)
+    return ctypes.c_void_p(raw(torch.cuda.current_device()))
 
 
 def _workspace(nbytes: int, device) -> torch.Tensor:

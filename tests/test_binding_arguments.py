@@ -49,3 +49,16 @@ def test_optional_tensors_become_null_pointers():
     assert c.w is None and c.w32 is None and c.mom32 is None and c.wall_normal is None
     c = operators(w=DeviceTensor(30, 64), wall_normal=DeviceTensor(4, 80))._c()
     assert (c.w, c.wall_normal) == (64, 80)
+
+
+def test_stream_without_the_raw_handle_function(monkeypatch):
+    """A torch that lacks its private function for the raw handle gives the
+    stream through the public one."""
+    torch = labfm.torch
+
+    class Stream:
+        cuda_stream = 1234
+
+    monkeypatch.delattr(torch._C, "_cuda_getCurrentRawStream", raising=False)
+    monkeypatch.setattr(torch.cuda, "current_stream", Stream)
+    assert labfm._stream().value == 1234

@@ -2288,14 +2288,18 @@ hipError_t launch_rows(const BuildArgs& g, const int* list, int count, hipStream
   return hipGetLastError();
 }
 
+// Solves sv.count systems in the kernel that builds as many nodes of order M.
 template <int M>
 hipError_t launch_solve(const SolveArgs& sv, hipStream_t st) {
   if constexpr (M <= kGroupMax) {
-    hipLaunchKernelGGL(group_solve_kernel<M>, dim3(blocks_for(sv.count, (GroupShape<M, LABFM_NUM_OPS>::G))),
-                       dim3(64), 0, st, sv);
-  } else {
-    hipLaunchKernelGGL(rows_solve_kernel<M>, dim3(sv.count), dim3(64), 0, st, sv);
+    if (sv.count >= kGroupMin) {
+      hipLaunchKernelGGL(group_solve_kernel<M>,
+                         dim3(blocks_for(sv.count, (GroupShape<M, LABFM_NUM_OPS>::G))), dim3(64), 0,
+                         st, sv);
+      return hipGetLastError();
+    }
   }
+  hipLaunchKernelGGL(rows_solve_kernel<M>, dim3(sv.count), dim3(64), 0, st, sv);
   return hipGetLastError();
 }
 

@@ -2340,13 +2340,11 @@ struct OptArgs {
   const double* x;
   const double* y;
   const double* s;
-  const int8_t* order;
   labfm_box box;
   const int* row_ptr;  // CSR of the h0 stencils
-  const int* row_end;  // this pass's rows: the neighbours still in reach
   const int* col;
-  int* reach;          // the next pass's neighbours and row ends (from row_ptr on)
-  int* reach_end;
+  int* reach;          // of each row, from row_ptr to reach_end, the neighbours
+  int* reach_end;      // still in reach: a pass's rows, then the next one's
   long long nnz;
   const double* w;        // this pass's weights, rows x, y, L ([3][nnz])
   const int8_t* status;   // this pass's build status
@@ -2378,6 +2376,36 @@ stencil_opt_init_kernel(const double* __restrict__ h0, int n, double* __restrict
   k[i] = 0;
   h_out[i] = h0[i];
   iters[i] = 0;
+}
+
+// Whether a neighbour at scaled offset (zx, zy) counts as in reach of the kernel
+// (2 h, and a margin past rounding): the weights of all others are zeros.
+__device__ __forceinline__ bool in_reach(double zx, double zy) {
+  return !(zx * zx + zy * zy >= 4.0 * (1.0 + 1e-8));
+}
+
+// The first pass's lists: of every row, the neighbours in reach of h0. A row
+// may list more of them; left in, their zero weights would shift the others to
+// other lanes of the test and so round its sums otherwise. One wavefront per
+// node, once per call: 10 us for 16,384 nodes of K = 98.
+__global__ void __launch_bounds__(256)
+stencil_reach_kernel(OptArgs a, int n) {
+  const int i = blockIdx.x * 4 + (threadIdx.x >> 6), lane = threadIdx.x & 63;
+  if (i >= n) return;
+  const int e0 = uniform(a.row_ptr[i]), e1 = uniform(a.row_ptr[i + 1]);
+  const double hinv = 1.0 / a.h[i], xi = a.x[i], yi = a.y[i];
+  int kept = 0;
+  for (int k0 = e0; k0 < e1; k0 += 64) {
+    const bool have = k0 + lane < e1;
+    const int j = have ? a.col[k0 + lane] : i;
+    const double dx = wrap_axis(a.x[j] - xi, a.box.Lx, a.box.periodic_x);
+    const double dy = wrap_axis(a.y[j] - yi, a.box.Ly, a.box.periodic_y);
+    const bool keep = have && in_reach(dx * hinv, dy * hinv);
+    const unsigned long long mask = __builtin_amdgcn_ballot_w64(keep);
+    if (keep) a.reach[e0 + kept + __builtin_popcountll(mask & ((1ull << lane) - 1))] = j;
+    kept += __builtin_popcountll(mask);
+  }
+  if (lane == 0) a.reach_end[i] = e0 + kept;
 }
 
 // a's sum over lanes l and l ^ D in the lanes with bit D clear, b's in the
@@ -2436,7 +2464,12 @@ __device__ __forceinline__ double halves_sum(double a, double b, int lane) {
 // The test also lists the neighbours still in reach for the next pass: at
 // h/s = 1.6 two thirds of the h0 stencil carry zero weights, which a pass then
 // neither assembles nor tests (16,384 nodes of order 6: 16.3 -> 13.7 ms for
-// all passes; each sum keeps its order, so the counts are the same).
+// all passes). The assembly's and the residual's sums keep their order. The
+// amplitude sums do not: a neighbour's lane is its place in the list. A list is
+// a function of its node's neighbours in reach alone, so that a node's result
+// does not depend on what else its row holds; against sums over whole rows, a
+// node whose response lies within rounding of gain_max may take another count
+// (none did on 15 sets of 4,096 to 65,536 nodes).
 //
 // list: the nodes of order M still shrinking; goes_on[k] says whether list[k]
 // shrinks further.
@@ -2452,7 +2485,7 @@ stencil_accept_kernel(OptArgs a, const int* __restrict__ list, int count,
   const int i = uniform(list[kn]);
   const int lane = threadIdx.x;
   const int e0 = uniform(a.row_ptr[i]);
-  const int K = uniform(a.row_end[i]) - e0;
+  const int K = uniform(a.reach_end[i]) - e0;
   const int kcur = uniform(a.k[i]);
   const double h = a.h[i], s = a.s[i], xi = a.x[i], yi = a.y[i];
   const int px = a.box.periodic_x, py = a.box.periodic_y;
@@ -2472,7 +2505,7 @@ stencil_accept_kernel(OptArgs a, const int* __restrict__ list, int count,
   double xn = 0.0, yn = 0.0, wn[3] = {0.0, 0.0, 0.0};
   auto fetch = [&](int k) {
     if (k < K) {
-      jn = a.col[e0 + k];
+      jn = a.reach[e0 + k];
       xn = a.x[jn];
       yn = a.y[jn];
 #pragma unroll
@@ -2493,11 +2526,10 @@ stencil_accept_kernel(OptArgs a, const int* __restrict__ list, int count,
     }
     {
       const double zx = dx * hinv, zy = dy * hinv;
-      // Out of the kernel's reach (2 h, and by a margin past rounding) at this
-      // scale is out of reach at every smaller one: its weights are zeros, and
-      // the next pass goes without it. The list may be this pass's own: what
-      // this round writes lies before what the prefetch above has read.
-      const bool keep = have && !(zx * zx + zy * zy >= 4.0 * (1.0 + 1e-8));
+      // Out of reach at this scale is out of reach at every smaller one: the
+      // next pass goes without it. The list is this pass's own: what this round
+      // writes lies before what the prefetch above has read.
+      const bool keep = have && in_reach(zx, zy);
       const unsigned long long mask = __builtin_amdgcn_ballot_w64(keep);
       if (keep) a.reach[e0 + kept + __builtin_popcountll(mask & ((1ull << lane) - 1))] = j;
       kept += __builtin_popcountll(mask);
@@ -3172,10 +3204,8 @@ extern "C" int labfm_optimise_stencils(const double* x, const double* y, const d
   a.x = x;
   a.y = y;
   a.s = s;
-  a.order = order_m;
   a.box = box;
   a.row_ptr = row_ptr;
-  a.row_end = row_ptr + 1;
   a.col = col;
   a.reach = reinterpret_cast<int*>(base + L.reach);
   a.reach_end = reinterpret_cast<int*>(base + L.reach_end);
@@ -3193,8 +3223,10 @@ extern "C" int labfm_optimise_stencils(const double* x, const double* y, const d
   hipLaunchKernelGGL(stencil_opt_init_kernel, dim3(blocks_for(n, 256)), dim3(256), 0, st, h0, n,
                      a.h, a.k, a.h_out, a.iters);
   LABFM_HIP(hipGetLastError());
+  hipLaunchKernelGGL(stencil_reach_kernel, dim3(blocks_for(n, 4)), dim3(256), 0, st, a, n);
+  LABFM_HIP(hipGetLastError());
   // x, y and L weights of the nodes still shrinking, at their current scales
-  BuildArgs g{x, y, a.h, s, order_m, n, box, row_ptr, row_ptr + 1, col, nnz,
+  BuildArgs g{x, y, a.h, s, order_m, n, box, row_ptr, a.reach_end, a.reach, nnz,
               reinterpret_cast<double*>(base + L.w), nullptr, nullptr,
               reinterpret_cast<double*>(base + L.kappa), nullptr,
               reinterpret_cast<int8_t*>(base + L.status),
@@ -3232,9 +3264,6 @@ extern "C" int labfm_optimise_stencils(const double* x, const double* y, const d
     }
     LABFM_HIP(hipMemcpyAsync(left, counts, sizeof(left), hipMemcpyDeviceToHost, st));
     LABFM_HIP(hipStreamSynchronize(st));
-    // from the second pass on, the neighbours that were in reach in the one before
-    g.row_end = a.row_end = a.reach_end;
-    g.col = a.col = a.reach;
   }
   set_error("optimise_stencils: %s", "nodes still shrinking after max_iter + 2 passes");
   return LABFM_ERR_HIP;

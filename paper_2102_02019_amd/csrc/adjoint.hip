@@ -406,14 +406,32 @@ extern "C" int labfm_build_transpose(const labfm_operators* ops, int32_t* tptr, 
   return LABFM_OK;
 }
 
+namespace labfm {
+namespace {
+// Doubles per node of a reversed step's registers. The most that is live at one
+// time, in the filter's gather, fills them; what comes later lies where
+// something has been read for the last time:
+//   sums of stages 1..4   then the operator-sum adjoints of stages 3 and 1
+//                         (g[0]) over those of stage 4
+//   g[1], loc[1]          the adjoints of stages 4 and 2, their pointwise terms
+//   kq                    kappa qbar
+//   qbar                  then Ybar_4, then the step's result
+//   Y2                    then Ybar_2; the forward steps' register
+//   Y3                    then Ybar_3; the forward steps' other register
+//   Y4                    then loc[0]
+//   qs                    the recomputed step's q, then P
+// No kernel writes what it also reads.
+constexpr int kAdjRegs = 4 * kStageSums + kAdj + 3 + 4 + 5 * 3;
+static_assert(kAdj <= kStageSums && kStageSums % 2 == 0 && kAdj % 2 == 0,
+              "g[0] in the sums of a stage, all on 16 bytes");
+}  // namespace
+}  // namespace labfm
+
 extern "C" size_t labfm_adjoint_workspace_bytes(int32_t n, int32_t n_steps, int32_t ckpt_every) {
   if (n <= 0 || n_steps < 0 || ckpt_every <= 0) return 0;
-  const long long nck = ceil_div(n_steps, ckpt_every) + 1;
-  // checkpoints, one recomputed segment, and the registers of a reversed step:
-  // ten of 3 n doubles, the stages' sums, two sets of operator-sum adjoints
-  // with their pointwise terms, kappa qbar
-  const long long per_node = 10 * 3 + 4 * kStageSums + 2 * (kAdj + 3) + 4;
-  const long long doubles = 3LL * n * (nck + ckpt_every) + per_node * n;
+  // checkpoints, one recomputed segment, and a reversed step's registers
+  const long long nck = ceil_div(n_steps, ckpt_every);
+  const long long doubles = 3LL * n * (nck + ckpt_every) + static_cast<long long>(kAdjRegs) * n;
   return static_cast<size_t>(doubles) * sizeof(double) + 512;
 }
 
@@ -440,27 +458,25 @@ extern "C" int labfm_rk_adjoint(const double* q0, const double* qbar_end, double
   hipStream_t st = as_stream(stream_);
   const long long N3 = 3LL * n;
   const size_t b3 = sizeof(double) * N3;
-  const long long nck = ceil_div(n_steps, ckpt_every) + 1;
-  // the records read with 16-byte loads first, on a 16-byte boundary
+  // kAdjRegs says what lies where; the records read with 16-byte loads first, on
+  // a 16-byte boundary
   double* sums = reinterpret_cast<double*>((reinterpret_cast<uintptr_t>(workspace) + 15) &
                                            ~static_cast<uintptr_t>(15));
   double* g[2];
-  g[0] = sums + 4LL * kStageSums * n;
-  g[1] = g[0] + static_cast<long long>(kAdj) * n;
+  g[0] = sums + 3LL * kStageSums * n;
+  g[1] = sums + 4LL * kStageSums * n;
   double* kq = g[1] + static_cast<long long>(kAdj) * n;
-  double* loc[2] = {kq + 4LL * n, kq + 4LL * n + N3};
-  double* ck = loc[1] + N3;
-  double* seg = ck + nck * N3;
-  double* Y2 = seg + static_cast<long long>(ckpt_every) * N3;
+  double* loc[2];
+  loc[1] = kq + 4LL * n;
+  double* qbar = loc[1] + N3;
+  double* Y2 = qbar + N3;
   double* Y3 = Y2 + N3;
   double* Y4 = Y3 + N3;
   double* qs = Y4 + N3;
-  double* Ra = qs + N3;
-  double* Rb = Ra + N3;
-  double* qbar = Rb + N3;
-  double* P = qbar + N3;
-  double* Ba = P + N3;
-  double* Bb = Ba + N3;
+  double* ck = qs + N3;
+  double* seg = ck + ceil_div(n_steps, ckpt_every) * N3;
+  loc[0] = Y4;
+  double* P = qs;
 
   const Flow fl{prm->c2, prm->mu, prm->gx, prm->gy};
   const double dt = prm->dt;
@@ -473,8 +489,8 @@ extern "C" int labfm_rk_adjoint(const double* q0, const double* qbar_end, double
   plan.fl = fl;
   plan.dt = dt;
   plan.filter = prm->filter;
-  plan.Ya = Ra;
-  plan.Yb = Rb;
+  plan.Ya = Y2;
+  plan.Yb = Y3;
   const LaunchCfg scfg = plan.stage_cfg;
   const long long nnz = ops->nnz;
   const unsigned grid = blocks_for(static_cast<long long>(n) * kAdjLpn, 256);
@@ -552,11 +568,11 @@ extern "C" int labfm_rk_adjoint(const double* q0, const double* qbar_end, double
                            next(3));
       }
       LABFM_LAUNCHED();
-      // stages 4 .. 1 (index i = 3 .. 0): Ybar_4 -> Ba, Ybar_3 -> Bb,
-      // Ybar_2 -> Ba. Stage index i's transposed gather folds Ybar_{i+1} into
-      // P (P_2 = P_3 + Ybar_4, P_1 = P_2 + Ybar_3) before the pointwise part
-      // of stage i - 1; the last one leaves qbar = P_1 + Ybar_2 + Ybar_1.
-      double* out[4] = {nullptr, Ba, Bb, Ba};
+      // stages 4 .. 1 (index i = 3 .. 0), Ybar_{i+1} to out[i]. Stage index
+      // i's transposed gather folds Ybar_{i+2} into P (P_2 = P_3 + Ybar_4,
+      // P_1 = P_2 + Ybar_3) before the pointwise part of stage i - 1; the last
+      // one leaves qbar = P_1 + Ybar_2 + Ybar_1.
+      double* out[4] = {nullptr, Y2, Y3, qbar};
       for (int i = 3; i >= 0; --i) {
         hipLaunchKernelGGL(transpose, dim3(grid), dim3(256), 0, st, tr->tptr, tr->tsrc, tr->tw, nnz,
                            tr->rowsum, g[i % 2], loc[i % 2], n, out[i], P,

@@ -723,8 +723,8 @@ def adjoint_bench(args, inputs, labfm, torch, np, dev, ckpt_every=20):
     200 steps, a checkpoint every 20 steps): forward run, then the gradient
     of a scalar loss of the final state with respect to the initial state
     (labfm_rk_adjoint: each checkpoint segment recomputed once, then per step
-    the filter adjoint and four stage adjoints, each a forward gather and a
-    transposed gather). Inputs resident on the device. Reports the adjoint's
+    its four stages once more, which store their operator sums, the filter
+    adjoint and four stage adjoints, each a transposed gather). Inputs resident on the device. Reports the adjoint's
     node-updates/s (N x 4 stages x steps / its time), its cost relative to the
     forward run, and the pass's algorithmic bytes per second. At this size a
     stage's data (~180 MB) stays in the 256 MB last-level cache, so the rate is
@@ -771,11 +771,14 @@ def adjoint_bench(args, inputs, labfm, torch, np, dev, ckpt_every=20):
     fwd, adj = sum(fwd_ms) / len(fwd_ms), sum(adj_ms) / len(adj_ms)
     kbar = ops.nnz / N
     # algorithmic bytes per node and step: the recomputed forward step
-    # (4 stages of 44K + 104 and a filter of 12K + 56), four forward gathers
-    # (44K + 216) and four transposed gathers (44K + 240), and the filter
-    # adjoint (12K + 80)
-    per_node_step = (4 * (44 * kbar + 104) + 12 * kbar + 56 + 4 * (44 * kbar + 216)
-                     + 4 * (44 * kbar + 240) + 12 * kbar + 80)
+    # (4 stages of 44K + 104 and a filter of 12K + 56), its stages again with
+    # 64 bytes of operator sums each (44K + 168), four transposed gathers with
+    # the pointwise part of the next stage (44K + 376: the row start 8, six
+    # adjoints 48, pointwise terms 24, P read and written 48, Ybar read and
+    # written 48, row sums 40, then Y 24, sums 64, adjoints 48 and pointwise
+    # terms 24) and the filter adjoint with that of the last stage (12K + 256)
+    per_node_step = (4 * (44 * kbar + 104) + 12 * kbar + 56 + 4 * (44 * kbar + 168)
+                     + 4 * (44 * kbar + 376) + 12 * kbar + 256)
     achieved = per_node_step * N * steps / (adj * 1e-3) / 1e9
     return {
         "metric": "adjoint of the filtered RK loop: node-updates/s (N x 4 stages x steps / time)",

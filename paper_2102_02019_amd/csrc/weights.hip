@@ -1911,11 +1911,15 @@ __device__ __forceinline__ void rows_node(BuildArgs g, const int* __restrict__ l
 // the registers.
 
 constexpr int kGroupMax = 6;  // highest order built this way
-// Fewest nodes of an order built this way: below two rounds of one-node
-// wavefronts (4,096 in flight each) those finish sooner (kernel and sorting,
-// m = 4, 5, 6 at 2,025 nodes: 61, 70, 81 us against 71, 86, 106; at 6,400: 86,
-// 110, 138 against 81, 106, 135, but 88 against 100 us for 5,890 nodes of order
-// 6 among others; at 8,281: 95, 127, 161 against 86, 117, 154).
+// Fewest nodes of an order built this way. A lone order gains from somewhere
+// between 2,025 and 6,400 nodes on (kernel and sorting, m = 4, 5, 6, one node a
+// wavefront against this: 61, 70, 81 us against 71, 86, 106 at 2,025 nodes; 86,
+// 110, 138 against 81, 106, 135 at 6,400; 95, 127, 161 against 86, 117, 154 at
+// 8,281). The line lies at two rounds of one-node wavefronts (4,096 in flight
+// each) for the sets that hold other orders too, where fewer and longer
+// wavefronts end last: 5,890 nodes of order 6 among 40,000 took 88 us in
+// wavefronts of their own and 100 us shared. A lone order of 6,400 nodes loses
+// 2 to 6% by it.
 constexpr int kGroupMin = 8192;
 
 template <int M, int NOPS>
@@ -2272,7 +2276,8 @@ rows_solve_kernel(SolveArgs sv) {
   rows_node<M, true>(BuildArgs{}, nullptr, sv.count, sv);
 }
 
-// Builds `count` nodes of order M with NOPS operators.
+// Builds `count` nodes of order M: with NOPS operators in shared wavefronts, all
+// six in wavefronts of their own (the rows that g leaves out are not written).
 template <int M, int NOPS>
 hipError_t launch_rows(const BuildArgs& g, const int* list, int count, hipStream_t st) {
   if (count <= 0) return hipSuccess;
